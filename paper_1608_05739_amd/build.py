@@ -18,8 +18,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libpsatd.so")
-SOURCES = ["kernels.hip", "fast2d.hip", "wave2d.hip", "wavex.hip", "wave3d.hip", "domain.hip",
-           "fdtd.hip", "api.cpp"]
+SOURCES = ["lines_large.hip", "lines_long.hip", "lines_mid.hip", "lines_small.hip", "lines.hip",
+           "kernels.hip", "fast2d.hip", "wave2d.hip", "wave3d.hip", "domain.hip", "fdtd.hip", "api.cpp"]
 
 ARCH = os.environ.get("PSATD_OFFLOAD_ARCH", "gfx950")
 
@@ -53,7 +53,7 @@ def _compile(src, verbose):
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
         results = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
     if verbose:
         for _obj, err in results:

@@ -16,6 +16,7 @@
 #include "fast2d.hpp"
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "lines.hpp"
 #include "psatd.h"
 #include "update.hpp"
 #include "wave2d.hpp"
@@ -144,8 +145,7 @@ struct DeviceGuard {
 enum PassType { kLine = 0, kFused = 1, kUpdate = 2, kFastXFwd = 3, kFastZ = 4, kFastXInv = 5,
                 kWaveZ = 6, kWaveX = 7 };
 
-// One launch of a pass compiled per length (compile-time line passes, the
-// wave-resident x passes): the work items of one line length.
+// One launch of a pass compiled per length: the work items of one line length.
 struct SubLaunch {
   int L = 0;
   int first = 0;  // index of its first work item within the pass's list
@@ -171,12 +171,11 @@ struct Pass {
   std::vector<int> comps;  // line passes: the components they transform
   int lines = 0;           // line passes: lines per workgroup (the tile)
   int region = 0;          // wave-resident passes: double2 elements of LDS per wavefront
-  bool ct = false;         // line passes: the compile-time-length kernels (ct_line_kernel),
-  std::vector<SubLaunch> subs;  // ct line and wave x passes: one launch per length
+  std::vector<SubLaunch> subs;  // passes compiled per length: one launch per length
 };
 
-// One pass's choice in a tuning string: pass type, compile-time flag, lines
-// per workgroup, modes per thread, points per thread, grid (-1: the plan's
+// One pass's choice in a tuning string: pass type, a flag that earlier versions
+// set for their compile-time line kernels (0 now), lines per workgroup, modes per thread, points per thread, grid (-1: the plan's
 // default grid).
 struct Choice {
   int type, ct, lines, mpt, ppt, grid;
@@ -405,141 +404,44 @@ int line_ppt(const psatd_plan_s* plan) {
   return (plan->cfg.flags & PSATD_FLAG_RADIX4_LINES) ? 4 : kMaxPts;
 }
 
-// Lines of a line pass between which a tile of the compile-time kernels may
-// not cross: the strided side of the x and y passes is placed by one division
-// per tile (the tile map's A), so a tile stays inside one run of A lines.
-int tile_period(int kind, const PatchDev& P) {
-  if (kind == kXFwd || kind == kXInv) return P.ndim == 2 ? P.nz : P.ny;
-  if (kind == kYFwd || kind == kYInv) return P.nz;
-  return 0;
+// Line length, lines, and the run of lines a tile stays in, of the line passes
+// with compile-time lengths (lines.hpp): x rows (L = nx / 2) in runs of nz (2D)
+// or ny (3D) rows; y lines (L = ny) l = kx nz + z in runs of nz; z lines anywhere.
+void fixed_line_geometry(int kind, const PatchDev& P, int* L, int* nlines, int* run) {
+  line_geometry(kind, P, nlines, L);
+  if (kind == kXFwd || kind == kXInv) *run = P.ndim == 2 ? P.nz : P.ny;
+  else if (kind == kYFwd || kind == kYInv) *run = P.nz;
+  else *run = *nlines;
 }
 
-// The compile-time line kernels take every patch of the plan if each line
-// length is compiled.
-bool ct_line_eligible(int kind, const psatd_plan_s* plan) {
-  // (PSATD_FLAG_RADIX4_LINES asks for the generic radix-4 schedule)
-  if (plan->cfg.flags & (PSATD_FLAG_GENERIC_KERNELS | PSATD_FLAG_RADIX4_LINES)) return false;
-  if (!plan->maps.empty() && (kind == kXFwd || kind == kXInv)) return false;  // (see GlobalMap)
-  for (const PatchDev& P : plan->host_patches) {
-    int nlines, L;
-    line_geometry(kind, P, &nlines, &L);
-    if (!ct_line_supported(L)) return false;
-  }
-  return true;
-}
-
-Pass make_ct_line_pass(int kind, const psatd_plan_s* plan, const std::vector<int>& comps,
-                       std::vector<WorkItem>& items) {
-  Pass ps;
-  ps.type = kLine;
-  ps.ct = true;
-  ps.line_kind = kind;
-  ps.ppt = 0;
-  ps.name = line_pass_name(kind);
-  size_t lds = 0;
-  const size_t first = items.size();
-  double bytes = 0.0;
-  std::set<int> lengths;
-  for (const PatchDev& P : plan->host_patches) {
-    int nlines, L;
-    line_geometry(kind, P, &nlines, &L);
-    lengths.insert(L);
-  }
-  for (int Lc : lengths) {
-    SubLaunch sub;
-    sub.L = Lc;
-    sub.first = static_cast<int>(items.size() - first);
-    for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
-      const PatchDev& P = plan->host_patches[pi];
-      int nlines, L;
-      line_geometry(kind, P, &nlines, &L);
-      if (L != Lc) continue;
-      const int R = std::min(ct_line_tile(L), nlines);
-      ps.lines = std::max(ps.lines, R);
-      // tiles of R lines inside each run of A lines (the last one shorter
-      // where R does not divide A)
-      const int A = tile_period(kind, P) > 0 ? tile_period(kind, P) : nlines;
-      for (int c : comps)
-        for (int a0 = 0; a0 < nlines; a0 += A)
-          for (int l = a0; l < std::min(a0 + A, nlines); l += R)
-            items.push_back(
-                WorkItem{static_cast<int>(pi), l, std::min(R, std::min(a0 + A, nlines) - l), c});
-      const double cells = static_cast<double>(P.nx) * P.ny * P.nz;
-      bytes += comps.size() * 2.0 * cells * plan->elem;
-    }
-    sub.nitems = static_cast<int>(items.size() - first) - sub.first;
-    const size_t sub_lds = static_cast<size_t>(lpad_size(ct_line_tile(Lc) * Lc)) * sizeof(double2);
-    sub.shape = LaunchShape{sub.nitems, kCtBlock, sub_lds};
-    lds = std::max(lds, sub_lds);
-    ps.subs.push_back(sub);
-  }
-  ps.nitems = static_cast<int>(items.size() - first);
-  ps.shape = LaunchShape{ps.nitems, kCtBlock, lds};
-  ps.bytes = bytes;
-  ps.comps = comps;
-  ps.d_items = reinterpret_cast<WorkItem*>(first);
-  return ps;
-}
-
-// Wave-resident x passes (wavex.hip): 2D or 3D, FP32 storage, every row
-// length compiled.  (PSATD_FLAG_RADIX4_LINES asks for the generic radix-4
+// The compile-time line passes take every patch of the plan if each line
+// length is compiled.  (PSATD_FLAG_RADIX4_LINES asks for the generic radix-4
 // schedule.)
-bool wave_x_eligible(const psatd_plan_s* plan) {
-  const psatd_config& c = plan->cfg;
-  if (c.flags & (PSATD_FLAG_GENERIC_KERNELS | PSATD_FLAG_RADIX4_LINES)) return false;
-  if (!plan->maps.empty()) return false;  // (see GlobalMap)
-  if (c.precision != PSATD_FP32) return false;
-  for (const PatchDev& P : plan->host_patches)
-    if (!wave2d::x_supported(P.mx)) return false;
-  return true;
-}
-
-// Wave-resident y passes (wavex.hip): 3D, FP32 storage, every y length
-// compiled.
-bool wave_y_eligible(const psatd_plan_s* plan) {
-  const psatd_config& c = plan->cfg;
-  if (c.flags & (PSATD_FLAG_GENERIC_KERNELS | PSATD_FLAG_RADIX4_LINES)) return false;
-  if (plan->ndim != 3 || c.precision != PSATD_FP32) return false;
-  for (const PatchDev& P : plan->host_patches)
-    if (!wave2d::x_supported(P.ny)) return false;
-  return true;
-}
-
-bool wave_line_eligible(int kind, const psatd_plan_s* plan) {
-  if (kind == kXFwd || kind == kXInv) return wave_x_eligible(plan);
-  if (kind == kYFwd || kind == kYInv) return wave_y_eligible(plan);
-  return false;
-}
-
-// Line length, lines, and the run of lines a tile stays in, of the
-// wave-resident x and y passes: x rows (L = nx / 2) in runs of nz (2D) or ny
-// (3D) rows; y lines (L = ny) l = kx nz + z in runs of nz.
-void wave_line_geometry(int kind, const PatchDev& P, int* L, int* nlines, int* run) {
-  if (kind == kYFwd || kind == kYInv) {
-    *L = P.ny;
-    *nlines = P.mx * P.nz;
-    *run = P.nz;
-  } else {
-    *L = P.mx;
-    *nlines = P.ny * P.nz;
-    *run = P.ndim == 2 ? P.nz : P.ny;
+bool fixed_line_eligible(int kind, const psatd_plan_s* plan) {
+  if (plan->cfg.flags & (PSATD_FLAG_GENERIC_KERNELS | PSATD_FLAG_RADIX4_LINES)) return false;
+  for (const PatchDev& P : plan->host_patches) {
+    int nlines, L;
+    line_geometry(kind, P, &nlines, &L);
+    if (!lines::supported(kind, L)) return false;
   }
+  return true;
 }
 
-// Work items of up to x_rows_per_item(L) consecutive lines of one component
-// inside one run (wave_line_geometry), one launch per line length.
-Pass make_wave_x_pass(int kind, const psatd_plan_s* plan, const std::vector<int>& comps,
-                      std::vector<WorkItem>& items) {
+// Work items of up to lines::rows() consecutive lines of one component inside
+// one run (fixed_line_geometry), one launch per line length.
+Pass make_fixed_line_pass(int kind, const psatd_plan_s* plan, const std::vector<int>& comps,
+                          std::vector<WorkItem>& items) {
   Pass ps;
   ps.type = kWaveX;
   ps.line_kind = kind;
   ps.name = line_pass_name(kind);
+  const int prec = plan->cfg.precision;
   const size_t first = items.size();
   double bytes = 0.0;
   std::set<int> lengths;
   for (const PatchDev& P : plan->host_patches) {
     int L, nl, run;
-    wave_line_geometry(kind, P, &L, &nl, &run);
+    fixed_line_geometry(kind, P, &L, &nl, &run);
     lengths.insert(L);
   }
   size_t lds = 0;
@@ -548,11 +450,11 @@ Pass make_wave_x_pass(int kind, const psatd_plan_s* plan, const std::vector<int>
     SubLaunch sub;
     sub.L = L;
     sub.first = static_cast<int>(items.size() - first);
-    const int T = wave2d::x_rows_per_item(L);
+    const int T = lines::rows(kind, prec, L);
     for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
       const PatchDev& P = plan->host_patches[pi];
       int Lp, nrows, A;
-      wave_line_geometry(kind, P, &Lp, &nrows, &A);
+      fixed_line_geometry(kind, P, &Lp, &nrows, &A);
       if (Lp != L) continue;
       for (int c : comps)
         for (int r0 = 0; r0 < nrows; r0 += A)
@@ -562,10 +464,10 @@ Pass make_wave_x_pass(int kind, const psatd_plan_s* plan, const std::vector<int>
       bytes += comps.size() * 2.0 * cells * plan->elem;
     }
     sub.nitems = static_cast<int>(items.size() - first) - sub.first;
-    const size_t sub_lds = wave2d::x_lds(L);
-    sub.shape = LaunchShape{sub.nitems, wave2d::x_block(L), sub_lds};
+    const size_t sub_lds = lines::lds_bytes(kind, prec, L);
+    sub.shape = LaunchShape{sub.nitems, lines::block(kind, prec, L), sub_lds};
     lds = std::max(lds, sub_lds);
-    block = std::max(block, wave2d::x_block(L));
+    block = std::max(block, sub.shape.block);
     ps.lines = std::max(ps.lines, T);
     ps.subs.push_back(sub);
   }
@@ -771,7 +673,7 @@ Pass make_update_pass(const psatd_plan_s* plan, std::vector<WorkItem>& items) {
 // within the per-thread register budget.
 psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkItem* items) {
   const int maxpts = ps.type == kFused ? kMaxPtsFused : ps.ppt;
-  if (ps.type == kLine && !ps.ct && !line_ppt_supported(ps.ppt))
+  if (ps.type == kLine && !line_ppt_supported(ps.ppt))
     return fail(PSATD_ERR_STATE, std::string(ps.name) + ": points per thread not compiled");
   for (int i = 0; i < ps.nitems; ++i) {
     const WorkItem& w = items[i];
@@ -792,21 +694,21 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
     }
     if (ps.type == kWaveX) {
       int L, nrows, A;
-      wave_line_geometry(ps.line_kind, P, &L, &nrows, &A);
-      if (!wave2d::x_supported(L) || ((ps.line_kind == kYFwd || ps.line_kind == kYInv) && P.ndim != 3))
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (wave): line length not compiled");
+      fixed_line_geometry(ps.line_kind, P, &L, &nrows, &A);
+      const int prec = plan->cfg.precision;
+      if (!lines::supported(ps.line_kind, L) ||
+          ((ps.line_kind == kYFwd || ps.line_kind == kYInv) && P.ndim != 3))
+        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (fixed length): line length not compiled");
       if (w.comp < 0 || w.comp >= plan->nin)
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (wave): bad component");
+        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (fixed length): bad component");
       if (w.count < 1 || w.first < 0 || w.first + w.count > nrows ||
-          w.count > wave2d::x_rows_per_item(L) || w.first / A != (w.first + w.count - 1) / A)
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (wave): item out of range");
+          w.count > lines::rows(ps.line_kind, prec, L) || w.first / A != (w.first + w.count - 1) / A)
+        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (fixed length): item out of range");
       bool in_sub = false;
       for (const SubLaunch& sub : ps.subs)
-        in_sub = in_sub ||
-                 (i >= sub.first && i < sub.first + sub.nitems && sub.L == L &&
-                  sub.shape.block == wave2d::x_block(L) && sub.shape.lds_bytes >= wave2d::x_lds(L));
+        in_sub = in_sub || (i >= sub.first && i < sub.first + sub.nitems && sub.L == L);
       if (!in_sub)
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (wave): item outside its length's launch");
+        return fail(PSATD_ERR_STATE, std::string(ps.name) + " (fixed length): item outside its length's launch");
       continue;
     }
     if (ps.type == kWaveZ) {
@@ -839,28 +741,6 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
     if (ps.type == kUpdate) {
       if (static_cast<long long>(w.first) + w.count > P.comp_stride)
         return fail(PSATD_ERR_STATE, "update: item past the spectrum");
-      continue;
-    }
-    if (ps.type == kLine && ps.ct) {
-      int nlines, L;
-      line_geometry(ps.line_kind, P, &nlines, &L);
-      bool in_sub = false;
-      for (const SubLaunch& sub : ps.subs)
-        in_sub = in_sub || (i >= sub.first && i < sub.first + sub.nitems && sub.L == L &&
-                            sub.shape.lds_bytes >= static_cast<size_t>(lpad_size(ct_line_tile(L) * L)) *
-                                                       sizeof(double2));
-      if (!in_sub) return fail(PSATD_ERR_STATE, std::string(ps.name) + ": item outside its length's launch");
-      if (!ct_line_supported(L)) return fail(PSATD_ERR_STATE, std::string(ps.name) + ": length not compiled");
-      if (w.comp < 0 || w.comp >= plan->nin)
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + ": bad component");
-      if (w.count < 1 || w.first < 0 || w.first + w.count > nlines || w.count > ct_line_tile(L))
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + ": item out of range");
-      const int A = tile_period(ps.line_kind, P);
-      if (A > 0 && w.first / A != (w.first + w.count - 1) / A)
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + ": tile straddles the tile map");
-      if (static_cast<size_t>(lpad_size(ct_line_tile(L) * L)) * sizeof(double2) > ps.shape.lds_bytes)
-        return fail(PSATD_ERR_STATE, std::string(ps.name) + ": item exceeds LDS");
-      if (ps.shape.block != kCtBlock) return fail(PSATD_ERR_STATE, std::string(ps.name) + ": bad block size");
       continue;
     }
     int nlines, L;
@@ -1077,15 +957,8 @@ psatd_status enqueue_pass(const psatd_plan_s* plan, const Pass& ps, const FieldP
   const Physics ph{plan->cfg.c, plan->cfg.eps0};
   switch (ps.type) {
     case kLine:
-      if (ps.ct) {
-        e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
-          return launch_ct_line(ps.line_kind, plan->cfg.precision, sub.L, sub.shape, t,
-                                plan->d_patches, ps.d_items + sub.first, sub.nitems, f, ws);
-        });
-      } else {
-        e = launch_line_pass(ps.line_kind, plan->cfg.precision, ps.ppt, ps.shape, s,
-                             plan->d_patches, ps.d_items, ps.nitems, f, ws);
-      }
+      e = launch_line_pass(ps.line_kind, plan->cfg.precision, ps.ppt, ps.shape, s,
+                           plan->d_patches, ps.d_items, ps.nitems, f, ws);
       break;
     case kFused:
       e = launch_fused_z(plan->cfg.precision, plan->ndim, plan->src_form, ps.mpt, ps.shape,
@@ -1097,8 +970,8 @@ psatd_status enqueue_pass(const psatd_plan_s* plan, const Pass& ps, const FieldP
       break;
     case kWaveX:
       e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
-        return wave2d::launch_x(ps.line_kind, sub.L, sub.shape, t, plan->d_patches,
-                                ps.d_items + sub.first, sub.nitems, f, ws);
+        return lines::launch(ps.line_kind, plan->cfg.precision, sub.L, sub.shape.grid, t,
+                             plan->d_patches, ps.d_items + sub.first, sub.nitems, f, ws);
       });
       break;
     case kWaveZ:
@@ -1299,28 +1172,23 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
   // per thread and radices up to 8 at 8; they round differently, and each
   // is checked against the oracle by the tests)
   // (the wave-resident z pass: also the generic fused pass, at every choice)
-  // (line passes: also the compile-time and the wave-resident kernels where
-  // they apply)
+  // (line passes: also the kernels with compile-time lengths where they apply)
   const bool linelike = ps.type == kLine || ps.type == kWaveX;
   std::vector<int> vars = {0};
   if (ps.type == kFused || ps.type == kWaveZ) vars = fused_mpt_choices(plan->cfg.precision, plan->ndim);
   if (linelike) vars = {4, kMaxPts};
   auto add = [&](Pass c, std::vector<WorkItem>& its) {
     for (const Cand& x : cands)
-      if (x.pass.type == c.type && x.pass.ct == c.ct && x.pass.lines == c.lines &&
+      if (x.pass.type == c.type && x.pass.lines == c.lines &&
           x.pass.mpt == c.mpt && x.pass.ppt == c.ppt)
         return;
     c.d_items = nullptr;
     if (verify_pass(plan, c, its.data()) != PSATD_OK) return;
     cands.push_back(Cand{c, std::move(its)});
   };
-  if (linelike && !(ps.type == kLine && ps.ct) && ct_line_eligible(ps.line_kind, plan)) {
+  if (linelike && ps.type != kWaveX && fixed_line_eligible(ps.line_kind, plan)) {
     std::vector<WorkItem> its;
-    add(make_ct_line_pass(ps.line_kind, plan, ps.comps, its), its);
-  }
-  if (linelike && ps.type != kWaveX && wave_line_eligible(ps.line_kind, plan)) {
-    std::vector<WorkItem> its;
-    add(make_wave_x_pass(ps.line_kind, plan, ps.comps, its), its);
+    add(make_fixed_line_pass(ps.line_kind, plan, ps.comps, its), its);
   }
   if (linelike || ps.type == kFused || ps.type == kWaveZ) {
     for (int m : vars) {
@@ -1386,6 +1254,33 @@ psatd_status upload_items(psatd_plan_s* plan, Cand& c, WorkItem** d) {
   return PSATD_OK;
 }
 
+// A choice of the compile-time line kernels as earlier versions saved it, with
+// the tiles that those kernels had (type kWaveX: waves of up to 64 / S rows, or
+// type kLine with the compile-time flag: 512 threads of 6 or 8 points): it
+// selects the present ones.
+bool earlier_fixed_line_choice(const psatd_plan_s* plan, const Pass& c, const Choice& ch) {
+  if (ch.mpt != 0 || ch.ppt != 0) return false;
+  int wave_rows = 0, block_rows = 0;
+  bool in_wave = plan->cfg.precision == PSATD_FP32 && c.line_kind != kZFwd && c.line_kind != kZInv;
+  bool in_block = true;
+  for (const PatchDev& P : plan->host_patches) {
+    int L, nlines, run;
+    fixed_line_geometry(c.line_kind, P, &L, &nlines, &run);
+    const bool listed = L == 32 || L == 48 || L == 64 || L == 96 || L == 128 || L == 192 ||
+                        L == 256 || L == 384 || L == 512 || L == 1024;
+    in_wave = in_wave && listed;
+    in_block = in_block && listed;
+    if (!listed) continue;
+    const int points = L % 3 == 0 ? 12 : (L == 1024 ? 16 : 8);
+    const int per_wave = 64 * points / L;
+    wave_rows = std::max(wave_rows, (per_wave <= 2 ? 8 : 4) * per_wave);
+    block_rows = std::max(block_rows, std::min(512 * (L % 3 == 0 ? 6 : 8) / L, nlines));
+  }
+  if (ch.type == kWaveX && ch.ct == 0) return in_wave && ch.lines == wave_rows;
+  if (ch.type == kLine && ch.ct == 1) return in_block && ch.lines == block_rows;
+  return false;
+}
+
 // Apply the choices of a tuning string (from psatd_plan_tuning of a plan with
 // the same configuration and patches): no timing launch.
 psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice) {
@@ -1400,8 +1295,9 @@ psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice)
     int pick = -1;
     for (size_t ci = 0; ci < cands.size() && pick < 0; ++ci) {
       const Pass& c = cands[ci].pass;
-      if (c.type == ch.type && static_cast<int>(c.ct) == ch.ct && c.lines == ch.lines &&
-          c.mpt == ch.mpt && c.ppt == ch.ppt)
+      if ((c.type == ch.type && ch.ct == 0 && c.lines == ch.lines && c.mpt == ch.mpt &&
+           c.ppt == ch.ppt) ||
+          (c.type == kWaveX && earlier_fixed_line_choice(plan, c, ch)))
         pick = static_cast<int>(ci);
     }
     if (pick < 0)
@@ -1701,9 +1597,8 @@ psatd_status build_plan(psatd_plan_s* plan) {
     // compile-time line kernels where every length is compiled, else the
     // generic ones (the autotuner times both)
     auto line = [&](int kind, const std::vector<int>& comps) {
-      if (wave_line_eligible(kind, plan)) return make_wave_x_pass(kind, plan, comps, items);
-      return ct_line_eligible(kind, plan) ? make_ct_line_pass(kind, plan, comps, items)
-                                          : make_line_pass(kind, plan, comps, items);
+      return fixed_line_eligible(kind, plan) ? make_fixed_line_pass(kind, plan, comps, items)
+                                             : make_line_pass(kind, plan, comps, items);
     };
     plan->passes.push_back(line(kXFwd, in_comps));
   if (plan->ndim == 3) plan->passes.push_back(line(kYFwd, in_comps));
@@ -1771,8 +1666,8 @@ psatd_status build_plan(psatd_plan_s* plan) {
                   ps.name, ps.nitems, ps.shape.grid, ps.shape.block, ps.shape.lds_bytes, ps.mpt,
                   ps.ppt, ps.lines, ps.bytes,
                   (ps.type == kWaveZ || ps.type == kWaveX)
-                      ? "wave"
-                      : (ps.ct ? "compile-time" : (ps.type >= kFastXFwd ? "4096" : "generic")),
+                      ? (cfg.precision == PSATD_FP32 ? "wave" : "compile-time")
+                      : (ps.type >= kFastXFwd ? "4096" : "generic"),
                   ps.tuning_applied ? " (tuning applied)" : (ps.tuned_ms >= 0.0 ? " (autotuned)" : ""));
     plan->info += buf;
   }
@@ -1805,7 +1700,6 @@ psatd_status create_plan(const psatd_config* cfg, const psatd_patch_desc* patche
         hipError_t e = configure_kernel_attributes();
         if (e == hipSuccess) e = fast2d::configure_attributes();
         if (e == hipSuccess) e = wave2d::configure_attributes();
-        if (e == hipSuccess) e = wave2d::configure_x_attributes();
         if (e == hipSuccess) e = wave2d::configure_z3_attributes();
         if (e != hipSuccess) return hip_fail(e, "kernel attributes");
         if (lookup_scratch(device) != PSATD_OK)
@@ -1874,7 +1768,7 @@ psatd_status psatd_plan_tuning(psatd_plan_t plan, char* buf, size_t len, size_t*
   char tok[96];
   for (const Pass& ps : plan->passes) {
     std::snprintf(tok, sizeof(tok), ";%d,%d,%d,%d,%d,%d", static_cast<int>(ps.type),
-                  ps.ct ? 1 : 0, ps.lines, ps.mpt, ps.ppt, ps.grid_choice);
+                  0, ps.lines, ps.mpt, ps.ppt, ps.grid_choice);
     t += tok;
   }
   if (needed) *needed = t.size() + 1;

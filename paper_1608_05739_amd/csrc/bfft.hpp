@@ -1,0 +1,457 @@
+// Compile-time FFTs of lines spread over the threads of a workgroup (gfx950).
+//
+// A line of L = P S points belongs to S threads; thread s holds the points
+// s + S m (m < P) in registers.  Each Stockham stage of radix R (R divides P)
+// runs P / R butterflies per thread: butterfly t is j = s + S t, it reads
+// x[j + q L/R] -- register t + q P/R of the thread --, multiplies by w^q with
+// w = exp(SIGN 2 pi i (j mod Ns) / (Ns R)), applies the DFT of length R and
+// produces y[(j - j mod Ns) R + j mod Ns + q Ns] (Ns = product of the radices
+// before the stage).  Between stages the threads exchange y through LDS and
+// read back y[s + S m].  Input and output are in natural order.
+//
+// What bounds these transforms on this chip, and what follows from it:
+// - An FP64 instruction issues every 4 cycles per SIMD, like any other.  The
+//   butterflies are radix 2 and 3 steps with the stage twiddle folded in:
+//   r = a + w b is four FMAs and a - w b = 2 a - r two more, so that a
+//   radix-8 butterfly with its seven twiddles takes 84 operations (108 as
+//   seven products, their powers and an untwiddled DFT of 8), a radix-16 one
+//   220 (288).
+// - LDS: a wave writes 16-byte elements at 13 cycles per instruction whatever
+//   the pattern (up to two lanes per bank), and reads them at 4 when the 64
+//   lanes are consecutive (measured).  Exchanges are therefore few: 16 points
+//   per thread do 256 points in one exchange where 8 points need two.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "fft.hpp"
+
+namespace psatd {
+namespace bfft {
+
+#define PSATD_HD __host__ __device__ __forceinline__
+
+// ------------------------------------------------------------------ constants
+// cos(pi m / 72) for the multiples that the radices use: 10, 15 and 22.5
+// degrees (m = 4, 6 and 9 per step), and 7.5 for the r2c post-twiddles (3), from
+// first-quadrant values so that the symmetries hold exactly.
+constexpr double cos_72(int m) {
+  m %= 144;
+  if (m < 0) m += 144;
+  if (m > 72) return cos_72(144 - m);
+  if (m > 36) return -cos_72(72 - m);
+  switch (m) {
+    case 0: return 1.0;
+    case 3: return 0.99144486137381041114;   // 7.5 degrees
+    case 4: return 0.98480775301220805937;   // 10
+    case 6: return 0.96592582628906828675;   // 15
+    case 8: return 0.93969262078590838405;   // 20
+    case 9: return 0.92387953251128675613;   // 22.5
+    case 12: return 0.86602540378443864676;  // 30
+    case 15: return 0.79335334029123516458;  // 37.5
+    case 16: return 0.76604444311897803520;  // 40
+    case 18: return 0.70710678118654752440;  // 45
+    case 20: return 0.64278760968653932632;  // 50
+    case 21: return 0.60876142900872063942;  // 52.5
+    case 24: return 0.5;                     // 60
+    case 27: return 0.38268343236508977173;  // 67.5
+    case 28: return 0.34202014332566873304;  // 70
+    case 30: return 0.25881904510252076235;  // 75
+    case 32: return 0.17364817766693034885;  // 80
+    case 33: return 0.13052619222005159155;  // 82.5
+    default: return m == 36 ? 0.0 : 2.0;     // (2: not a value of these radices)
+  }
+}
+constexpr double sin_72(int m) { return cos_72(36 - m); }
+
+constexpr bool unit_circle() {
+  for (int m = 0; m < 144; ++m)
+    if (m % 4 == 0 || m % 3 == 0) {
+      const double r = cos_72(m) * cos_72(m) + sin_72(m) * sin_72(m) - 1.0;
+      if (r > 4e-16 || r < -4e-16) return false;
+    }
+  return true;
+}
+static_assert(unit_circle() && cos_72(24) == 0.5 && sin_72(12) == 0.5, "cos / sin tables");
+
+// ------------------------------------------------------------------ butterflies
+PSATD_HD double2 c2(double x, double y) {
+  double2 v;
+  v.x = x;
+  v.y = y;
+  return v;
+}
+PSATD_HD double2 mul(double2 a, double2 b) {
+  return c2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
+PSATD_HD double2 sqr(double2 a) {
+  const double t = a.x * a.y;
+  return c2(fma(a.x, a.x, -a.y * a.y), t + t);
+}
+// a * exp(SIGN 2 pi i M / N)
+template <int N, int M, int SIGN>
+PSATD_HD double2 rot(double2 a) {
+  constexpr int m = 144 / N * M;
+  static_assert(144 % N == 0 && cos_72(m) <= 1.0, "constant twiddle");
+  if constexpr (M == 0) {
+    return a;
+  } else if constexpr (m == 18) {  // 45 degrees: one factor
+    constexpr double h = cos_72(18);
+    return SIGN > 0 ? c2((a.x - a.y) * h, (a.x + a.y) * h) : c2((a.x + a.y) * h, (a.y - a.x) * h);
+  } else {
+    constexpr double c = cos_72(m), s = SIGN * sin_72(m);
+    return c2(fma(a.x, c, -a.y * s), fma(a.x, s, a.y * c));
+  }
+}
+
+// a, b <- a + w b, a - w b
+PSATD_HD void bfly(double2& a, double2& b, double2 w) {
+  const double2 r = c2(fma(-w.y, b.y, fma(w.x, b.x, a.x)), fma(w.y, b.x, fma(w.x, b.y, a.y)));
+  b = c2(fma(2.0, a.x, -r.x), fma(2.0, a.y, -r.y));
+  a = r;
+}
+// a, b <- a + SIGN i w b, a - SIGN i w b
+template <int SIGN>
+PSATD_HD void bfly_i(double2& a, double2& b, double2 w) {
+  double2 t = SIGN > 0 ? c2(-b.y, b.x) : c2(b.y, -b.x);
+  bfly(a, t, w);
+  b = t;
+}
+PSATD_HD void bfly1(double2& a, double2& b) {
+  const double2 d = c2(a.x - b.x, a.y - b.y);
+  a = c2(a.x + b.x, a.y + b.y);
+  b = d;
+}
+template <int SIGN>
+PSATD_HD void bfly1_i(double2& a, double2& b) {
+  double2 t = SIGN > 0 ? c2(-b.y, b.x) : c2(b.y, -b.x);
+  bfly1(a, t);
+  b = t;
+}
+
+// x0, x1, x2 <- DFT of length 3 of (x0, u x1, u^2 x2) (T) or (x0, x1, x2)
+template <int SIGN, bool T>
+PSATD_HD void dft3(double2& x0, double2& x1, double2& x2, double2 u, double2 u2) {
+  constexpr double h = SIGN * 0.86602540378443864676;
+  double2 s, d;
+  if constexpr (T) {
+    const double2 b = mul(x2, u2);
+    s = c2(fma(-u.y, x1.y, fma(u.x, x1.x, b.x)), fma(u.y, x1.x, fma(u.x, x1.y, b.y)));
+    d = c2(fma(-2.0, b.x, s.x), fma(-2.0, b.y, s.y));
+  } else {
+    s = c2(x1.x + x2.x, x1.y + x2.y);
+    d = c2(x1.x - x2.x, x1.y - x2.y);
+  }
+  const double2 m = c2(fma(-0.5, s.x, x0.x), fma(-0.5, s.y, x0.y));
+  x0 = c2(x0.x + s.x, x0.y + s.y);
+  x1 = c2(fma(-h, d.y, m.x), fma(h, d.x, m.y));
+  x2 = c2(fma(h, d.y, m.x), fma(-h, d.x, m.y));
+}
+
+// In-place DFT of length R (natural order in and out) of a[q] u^q (T) or a[q]:
+// v[k] <- sum_q a[q] u^q exp(SIGN 2 pi i q k / R).  Decimation in time: the
+// halves (or thirds) are transforms with base u^2 (u^3), joined by butterflies
+// with the twiddles u W_R^k.
+template <int R, int SIGN, bool T>
+PSATD_HD void dft(double2 (&a)[R], double2 u) {
+  if constexpr (R == 1) {
+    return;
+  } else if constexpr (R == 3) {
+    dft3<SIGN, T>(a[0], a[1], a[2], u, T ? sqr(u) : u);
+  } else if constexpr (R % 2 == 1) {
+    static_assert(R == 9, "odd radix");
+    double2 y[3][3];
+    double2 u3 = u;
+    if constexpr (T) u3 = mul(sqr(u), u);
+    static_for<0, 3>([&](auto rc) __attribute__((always_inline)) {
+      constexpr int r = decltype(rc)::value;
+      for (int q = 0; q < 3; ++q) y[r][q] = a[r + 3 * q];
+      dft<3, SIGN, T>(y[r], u3);
+    });
+    static_for<0, 3>([&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (!T && k == 0) {
+        dft3<SIGN, false>(y[0][0], y[1][0], y[2][0], u, u);
+      } else {
+        constexpr double cs = cos_72(16 * k), sn = SIGN * sin_72(16 * k);
+        const double2 w = T ? rot<9, k, SIGN>(u) : c2(cs, sn);
+        constexpr double cs2 = cos_72(32 * k), sn2 = SIGN * sin_72(32 * k);
+        const double2 w2 = T ? sqr(w) : c2(cs2, sn2);
+        dft3<SIGN, true>(y[0][k], y[1][k], y[2][k], w, w2);
+      }
+    });
+    for (int r = 0; r < 3; ++r)
+      for (int k = 0; k < 3; ++k) a[k + 3 * r] = y[r][k];
+  } else {
+    constexpr int H = R / 2;
+    double2 e[H], o[H];
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+      e[q] = a[2 * q];
+      o[q] = a[2 * q + 1];
+    }
+    double2 u2 = u;
+    if constexpr (T && H > 1) u2 = sqr(u);
+    dft<H, SIGN, T>(e, u2);
+    dft<H, SIGN, T>(o, u2);
+    // twiddles u W_R^k; from k = R / 4 on they repeat with a factor SIGN i
+    constexpr int K = R % 4 == 0 ? R / 4 : H;
+    static_for<0, K>([&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (T) {
+        const double2 w = rot<R, k, SIGN>(u);
+        bfly(e[k], o[k], w);
+        if constexpr (K < H) bfly_i<SIGN>(e[k + K], o[k + K], w);
+      } else if constexpr (k == 0) {
+        bfly1(e[0], o[0]);
+        if constexpr (K < H) bfly1_i<SIGN>(e[K], o[K]);
+      } else {
+        constexpr double cs = cos_72(144 / R * k), sn = SIGN * sin_72(144 / R * k);
+        bfly(e[k], o[k], c2(cs, sn));
+        if constexpr (K < H) bfly_i<SIGN>(e[k + K], o[k + K], c2(cs, sn));
+      }
+    });
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      a[k] = e[k];
+      a[k + H] = o[k];
+    }
+  }
+}
+
+// ------------------------------------------------------------------ schedules
+// P points per thread and up to five radices, in the order of the stages.
+struct Radices {
+  int P, n, r[5];
+};
+
+// Schedules of the passes that hold one transform at a time.
+// Every radix divides P; the first radix divides S = L / P or is a multiple of
+// it, so that the padded exchange addresses are a thread base plus constants.
+constexpr Radices line_radices(int L) {
+  switch (L) {
+    case 16: return {8, 2, {8, 2}};
+    case 18: return {18, 1, {18}};
+    case 24: return {12, 2, {12, 2}};
+    case 32: return {8, 2, {8, 4}};
+    case 36: return {12, 2, {12, 3}};
+    case 48: return {12, 2, {12, 4}};
+    case 54: return {18, 2, {18, 3}};
+    case 64: return {8, 2, {8, 8}};
+    case 72: return {12, 2, {12, 6}};
+    case 96: return {24, 2, {12, 8}};
+    case 108: return {18, 2, {18, 6}};
+    case 128: return {16, 2, {16, 8}};
+    case 144: return {12, 2, {12, 12}};
+    case 162: return {18, 2, {18, 9}};
+    case 192: return {24, 2, {24, 8}};
+    case 216: return {6, 3, {6, 6, 6}};
+    case 256: return {16, 2, {16, 16}};
+    case 288: return {24, 2, {24, 12}};
+    case 324: return {18, 2, {18, 18}};
+    case 384: return {24, 3, {8, 8, 6}};
+    case 432: return {12, 3, {12, 12, 3}};
+    case 486: return {18, 3, {9, 18, 3}};
+    case 512: return {8, 3, {8, 8, 8}};
+    case 576: return {24, 2, {24, 24}};
+    case 648: return {18, 3, {18, 18, 2}};
+    case 768: return {24, 3, {8, 8, 12}};
+    case 864: return {24, 3, {12, 24, 3}};
+    case 972: return {18, 3, {18, 18, 3}};
+    case 1024: return {16, 3, {16, 16, 4}};
+    case 1152: return {24, 3, {24, 24, 2}};
+    case 1296: return {12, 4, {12, 12, 3, 3}};
+    case 1458: return {18, 3, {9, 18, 9}};
+    case 1536: return {24, 3, {8, 8, 24}};
+    case 1728: return {24, 3, {24, 24, 3}};
+    case 2048: return {16, 3, {16, 16, 8}};
+    default: return {0, 0, {0}};
+  }
+}
+
+// Schedules of the fused z passes, whose threads also hold a set of
+// transformed inputs: at most 12 points per thread.
+constexpr Radices fused_radices(int L) {
+  switch (L) {
+    case 32: return {8, 2, {8, 4}};
+    case 36: return {12, 2, {12, 3}};
+    case 48: return {12, 2, {12, 4}};
+    case 54: return {6, 3, {6, 3, 3}};
+    case 64: return {8, 2, {8, 8}};
+    case 72: return {12, 2, {12, 6}};
+    case 96: return {12, 3, {4, 12, 2}};
+    case 108: return {12, 3, {3, 12, 3}};
+    case 128: return {8, 3, {8, 4, 4}};
+    case 144: return {12, 2, {12, 12}};
+    case 162: return {6, 4, {6, 3, 3, 3}};
+    case 192: return {12, 3, {4, 12, 4}};
+    case 216: return {12, 3, {6, 12, 3}};
+    case 256: return {8, 3, {8, 8, 4}};
+    case 288: return {12, 3, {12, 12, 2}};
+    case 324: return {6, 4, {6, 6, 3, 3}};
+    case 384: return {12, 4, {4, 4, 4, 6}};
+    case 432: return {12, 3, {12, 12, 3}};
+    case 512: return {8, 3, {8, 8, 8}};
+    case 576: return {12, 3, {12, 12, 4}};
+    case 648: return {12, 4, {6, 12, 3, 3}};
+    case 768: return {12, 4, {4, 4, 4, 12}};
+    case 864: return {12, 3, {12, 12, 6}};
+    case 1024: return {8, 4, {8, 8, 4, 4}};
+    case 1152: return {12, 4, {12, 12, 4, 2}};
+    case 1296: return {12, 4, {12, 12, 3, 3}};
+    case 1536: return {12, 5, {4, 4, 6, 4, 4}};
+    case 1728: return {12, 3, {12, 12, 12}};
+    case 2048: return {8, 4, {8, 8, 8, 4}};
+    case 2304: return {12, 4, {12, 12, 4, 4}};
+    case 3072: return {12, 5, {4, 4, 4, 4, 12}};
+    case 4096: return {8, 4, {8, 8, 8, 8}};
+    default: return {0, 0, {0}};
+  }
+}
+
+template <int L_, bool FUSED>
+struct Sched {
+  static constexpr Radices rd = FUSED ? fused_radices(L_) : line_radices(L_);
+  static constexpr int L = L_;
+  static constexpr int P = rd.P;       // points per thread
+  static constexpr int S = L / P;      // threads per line
+  static constexpr int N = rd.n;       // stages
+  static constexpr bool kWave = 64 % S == 0;  // a line never leaves its wave
+  static constexpr int radix(int i) { return rd.r[i]; }
+  static constexpr int ns(int i) {  // product of the radices before stage i
+    int n = 1;
+    for (int j = 0; j < i; ++j) n *= rd.r[j];
+    return n;
+  }
+  static constexpr bool valid() {
+    if (P < 1 || L % P != 0 || ns(N) != L) return false;
+    for (int i = 0; i < N; ++i)
+      if (P % rd.r[i] != 0) return false;
+    return true;
+  }
+  // Padding of exchange i (after stage i): PAD elements after every D.  The
+  // first exchange writes with a stride of its radix: one element after each
+  // block of a radix that is a multiple of 4.  Blocks of Ns = 4 elements
+  // (R Ns apart) get four.  The others meet at most two lanes per bank, which
+  // costs a write nothing.
+  static constexpr int pad_d(int i) {
+    if (i == 0 && rd.r[0] % 4 == 0) return rd.r[0];
+    if (i > 0 && ns(i) == 4 && (S % (4 * rd.r[i]) == 0 || (4 * rd.r[i]) % S == 0)) return 4 * rd.r[i];
+    return L;
+  }
+  static constexpr int pad_n(int i) { return i == 0 ? 1 : 4; }
+  static constexpr int pa(int i, int e) { return e + (e / pad_d(i)) * pad_n(i); }
+  // elements of a line's LDS row, odd so that rows start in different banks
+  static constexpr int row() {
+    int m = L;
+    for (int i = 0; i + 1 < N; ++i) {
+      const int need = pa(i, L - 1) + 1;
+      if (need > m) m = need;
+    }
+    return m | 1;
+  }
+  static constexpr int kRow = row();
+  // Stockham output index of butterfly t, output q, thread s at stage i
+  static constexpr PSATD_HD int out(int i, int s, int t, int q) {
+    const int R = rd.r[i], n = ns(i);
+    const int j = s + S * t, k = j % n;
+    return (j - k) * R + k + q * n;
+  }
+  // The padded reads s + S m are a thread base plus a constant where the
+  // padding period divides S or S divides it; the writes of a butterfly stay
+  // inside one period by the choice of pad_d.
+  static constexpr bool separable() {
+    for (int i = 0; i + 1 < N; ++i) {
+      const int d = pad_d(i);
+      if (d != L && S % d != 0 && d % S != 0) return false;
+    }
+    return true;
+  }
+  // padded distance of consecutive outputs of a butterfly
+  static constexpr int step(int i) { return pa(i, out(i, 0, 0, 1)) - pa(i, out(i, 0, 0, 0)); }
+};
+
+// The thread's twiddle bases of stage I (exp(-2 pi i k / (Ns R)), one per
+// butterfly), from the plan's table tw[m] = exp(-2 pi i m / L).
+template <typename SC, int I>
+PSATD_HD int twiddle_index(int s, int t) {
+  return ((s + SC::S * t) % SC::ns(I)) * (SC::L / (SC::ns(I) * SC::radix(I)));
+}
+// Distinct bases of stage I: butterflies repeat with period Ns / S in t.
+template <typename SC, int I>
+constexpr int bases() {
+  constexpr int ns = SC::ns(I), bpt = SC::P / SC::radix(I);
+  if (ns == 1) return 0;
+  if (SC::S % ns == 0) return 1;
+  if (ns % SC::S == 0) return ns / SC::S < bpt ? ns / SC::S : bpt;
+  return bpt;
+}
+template <typename SC, int I>
+struct Base {
+  double2 w[bases<SC, I>() > 0 ? bases<SC, I>() : 1];
+  PSATD_HD void load(const double2* tw, int s) {
+#pragma unroll
+    for (int t = 0; t < bases<SC, I>(); ++t) w[t] = gload(tw, twiddle_index<SC, I>(s, t));
+  }
+};
+
+// Stage I on the thread's points: v[t + q P/R] is input q of butterfly t, and
+// output q after it.
+template <typename SC, int I, int SIGN>
+PSATD_HD void stage(double2 (&v)[SC::P], const Base<SC, I>& tb) {
+  constexpr int R = SC::radix(I), BPT = SC::P / R;
+#pragma unroll
+  for (int t = 0; t < BPT; ++t) {
+    double2 a[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) a[q] = v[t + q * BPT];
+    if constexpr (SC::ns(I) > 1) {
+      double2 u = tb.w[t % bases<SC, I>()];
+      if constexpr (SIGN > 0) u.y = -u.y;
+      dft<R, SIGN, true>(a, u);
+    } else {
+      dft<R, SIGN, false>(a, c2(1.0, 0.0));
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[t + q * BPT] = a[q];
+  }
+}
+
+// Exchange I: stage I's outputs into the line's LDS row, and the points of
+// stage I + 1 out of it.
+template <typename SC, int I>
+PSATD_HD void put(const double2 (&v)[SC::P], double2* row, int s) {
+  constexpr int R = SC::radix(I), BPT = SC::P / R, ns = SC::ns(I);
+  static_assert(SC::valid() && SC::separable(), "schedule");
+#pragma unroll
+  for (int t = 0; t < BPT; ++t) {
+    // the block of butterfly t is a constant where Ns divides S or S t
+    constexpr bool fixed = SC::S % ns == 0;
+    const int b = fixed ? SC::pa(I, SC::out(I, s, 0, 0)) + SC::pa(I, SC::out(I, 0, t, 0)) - SC::pa(I, 0)
+                        : SC::pa(I, SC::out(I, s, t, 0));
+#pragma unroll
+    for (int q = 0; q < R; ++q) row[b + q * SC::step(I)] = v[t + q * BPT];
+  }
+}
+template <typename SC, int I>
+PSATD_HD void get(double2 (&v)[SC::P], const double2* row, int s) {
+  const int b = SC::pa(I, s);
+#pragma unroll
+  for (int m = 0; m < SC::P; ++m) v[m] = row[b + SC::pa(I, SC::S * m)];
+}
+
+// Wave-level ordering of LDS traffic (a line inside one wave), or the
+// workgroup barrier.
+template <bool WAVE>
+__device__ __forceinline__ void sync() {
+  if constexpr (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+}  // namespace bfft
+}  // namespace psatd

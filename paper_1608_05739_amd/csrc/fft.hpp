@@ -38,7 +38,7 @@ __device__ __forceinline__ double2 mul_si(double2 a) {
 // which every LDS wait (lgkmcnt) would also wait for.  (The host pass of the
 // compiler, which never runs this, reads through the plain pointer.)
 template <typename T>
-__device__ __forceinline__ T gload(const T* p, int i) {
+__host__ __device__ __forceinline__ T gload(const T* p, int i) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const __attribute__((address_space(1))) T* g = (const __attribute__((address_space(1))) T*)p;
   return g[i];
@@ -49,7 +49,7 @@ __device__ __forceinline__ T gload(const T* p, int i) {
 
 // ------------------------------------------------------------------ static_for
 template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
+__host__ __device__ __forceinline__ void static_for(F&& f) {
   if constexpr (I < N) {
     f(std::integral_constant<int, I>{});
     static_for<I + 1, N>(f);

@@ -1,0 +1,66 @@
+// Line passes with compile-time lengths (lines_*.hip): tiles and launchers.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "bfft.hpp"
+#include "internal.hpp"
+#include "kernels.hpp"
+
+namespace psatd {
+namespace lines {
+
+// Lengths (complex points) the line passes are compiled for, by pass: the x
+// passes take L = nx / 2 (even, so that the r2c pairs split evenly), the y
+// and z passes the side itself.
+#define PSATD_LINE_SMALL(X) X(24) X(32) X(36) X(48) X(54) X(64) X(72) X(96) X(108) X(128)
+#define PSATD_LINE_MID(X) X(144) X(162) X(192) X(216) X(256) X(288) X(324) X(384)
+#define PSATD_LINE_LARGE(X) X(432) X(486) X(512) X(576) X(648) X(768) X(864) X(1024)
+#define PSATD_LINE_LONG(X) X(1152) X(1296) X(1536) X(1728) X(2048)
+
+// A tile is T rows (lines) of one component, transformed by T S threads.  The
+// x and y passes transpose: on the strided side of a tile T consecutive
+// elements are one run of 8 T (FP32) or 16 T bytes (FP64), so T is 16 or 8
+// (128 bytes) as long as two tiles fit a CU's LDS, half of that for longer
+// lines, and as few as fit for the longest.
+template <int L, int ELEM, bool TRANSPOSING>
+struct Tile {
+  using SC = bfft::Sched<L, false>;
+  static constexpr int rows() {
+    const int want = ELEM == 4 ? 16 : 8;
+    int t = want;
+    while (t > 1 && (t * SC::S > 512 || t * SC::kRow * 16 > 80 * 1024)) t /= 2;
+    if (TRANSPOSING)  // at least 64-byte runs where one tile fits the LDS
+      while (t < want / 2 && 2 * t * SC::S <= 1024 && 2 * t * SC::kRow * 16 <= 160 * 1024) t *= 2;
+    while (t * SC::S < 128 && 2 * t * SC::kRow * 16 <= 40 * 1024) t *= 2;  // short lines: two waves
+    return t;
+  }
+  static constexpr int T = rows();
+  static constexpr int NT = (T * SC::S + 63) / 64 * 64;  // threads per workgroup
+  static constexpr int kLds = T * SC::kRow;              // double2 elements
+};
+
+// Is L compiled for the pass kind?  Rows per tile and threads per workgroup.
+bool supported(int kind, int L);
+int rows(int kind, int precision, int L);
+int block(int kind, int precision, int L);
+int lds_bytes(int kind, int precision, int L);
+
+// One launch covers the work items of one length: tiles of up to rows()
+// consecutive lines inside one run of the spectra layout.
+hipError_t launch(int kind, int precision, int L, int grid, hipStream_t stream,
+                  const PatchDev* patches, const WorkItem* items, int nitems,
+                  const FieldPtrs& fields, void* ws);
+
+// One translation unit per group of lengths (see the lists above).
+#define PSATD_LINE_GROUP(name)                                                                     \
+  hipError_t launch_##name(int kind, int precision, int L, int grid, hipStream_t stream,           \
+                           const PatchDev* patches, const WorkItem* items, int nitems,             \
+                           const FieldPtrs& fields, void* ws)
+PSATD_LINE_GROUP(small);
+PSATD_LINE_GROUP(mid);
+PSATD_LINE_GROUP(large);
+PSATD_LINE_GROUP(long);
+
+}  // namespace lines
+}  // namespace psatd
