@@ -18,8 +18,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libpsatd.so")
-SOURCES = ["lines_large.hip", "lines_long.hip", "lines_mid.hip", "lines_small.hip", "lines.hip",
-           "kernels.hip", "fast2d.hip", "wave2d.hip", "wave3d.hip", "domain.hip", "fdtd.hip", "api.cpp"]
+SOURCES = ["zfused_c.hip", "zfused_d.hip", "zfused_b.hip", "zfused_e.hip", "zfused_a.hip",
+           "zfused_f.hip", "lines_large.hip", "lines_long.hip", "lines_mid.hip", "lines_small.hip",
+           "kernels.hip", "fast2d.hip", "lines.hip", "zfused.hip", "domain.hip", "fdtd.hip", "api.cpp"]
 
 ARCH = os.environ.get("PSATD_OFFLOAD_ARCH", "gfx950")
 

@@ -19,7 +19,7 @@
 #include "lines.hpp"
 #include "psatd.h"
 #include "update.hpp"
-#include "wave2d.hpp"
+#include "zfused.hpp"
 
 using namespace psatd;
 
@@ -152,7 +152,6 @@ struct SubLaunch {
   int nitems = 0;
   LaunchShape shape{};
   int full = 0;    // workgroups that give every wave its own work (0: nitems)
-  int region = 0;  // wave z pass: double2 elements of LDS per wavefront
 };
 
 struct Pass {
@@ -170,7 +169,6 @@ struct Pass {
   bool tuning_applied = false;  // chosen by a tuning string (psatd_plan_tuned)
   std::vector<int> comps;  // line passes: the components they transform
   int lines = 0;           // line passes: lines per workgroup (the tile)
-  int region = 0;          // wave-resident passes: double2 elements of LDS per wavefront
   std::vector<SubLaunch> subs;  // passes compiled per length: one launch per length
 };
 
@@ -712,29 +710,15 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
       continue;
     }
     if (ps.type == kWaveZ) {
-      if (P.ndim == 2 ? !wave2d::z_supported(P.nz) : !wave2d::z3_supported(P.nz))
-        return fail(PSATD_ERR_STATE, "z_fused (wave): z length not compiled");
+      if (!zfused::supported(plan->cfg.precision, P.ndim, plan->src_form, P.nz))
+        return fail(PSATD_ERR_STATE, "z_fused (fixed length): z length not compiled");
       if (w.count < 1 || w.first < 0 || w.first + w.count > P.mx * P.ny ||
-          w.count > wave2d::z_lines_per_item(P.nz))
-        return fail(PSATD_ERR_STATE, "z_fused (wave): item out of range");
-      if (P.ndim == 2) {
-        // each item in the launch of its z length, whose LDS holds a region
-        // of that length per wavefront
-        bool in_sub = false;
-        for (const SubLaunch& sub : ps.subs)
-          in_sub = in_sub ||
-                   (i >= sub.first && i < sub.first + sub.nitems && sub.L == P.nz &&
-                    sub.region >= wave2d::z_region(P.nz) && sub.shape.block == wave2d::kBlock &&
-                    static_cast<size_t>(sub.region) * wave2d::kWavesPerBlock * sizeof(double2) <=
-                        sub.shape.lds_bytes);
-        if (!in_sub) return fail(PSATD_ERR_STATE, "z_fused (wave): item outside its length's launch");
-        continue;
-      }
-      if ((P.ndim == 2 ? wave2d::z_region(P.nz) : wave2d::z3_region(P.nz)) > ps.region ||
-          static_cast<size_t>(ps.region) * wave2d::kWavesPerBlock * sizeof(double2) > ps.shape.lds_bytes)
-        return fail(PSATD_ERR_STATE, "z_fused (wave): LDS region too small");
-      if (ps.shape.block != wave2d::kBlock)
-        return fail(PSATD_ERR_STATE, "z_fused (wave): bad block size");
+          w.count > zfused::lines_per_item(P.nz))
+        return fail(PSATD_ERR_STATE, "z_fused (fixed length): item out of range");
+      bool in_sub = false;
+      for (const SubLaunch& sub : ps.subs)
+        in_sub = in_sub || (i >= sub.first && i < sub.first + sub.nitems && sub.L == P.nz);
+      if (!in_sub) return fail(PSATD_ERR_STATE, "z_fused (fixed length): item outside its length's launch");
       continue;
     }
     if (w.count < 1 || w.first < 0) return fail(PSATD_ERR_STATE, std::string(ps.name) + ": empty item");
@@ -837,85 +821,60 @@ Pass make_fast_pass(PassType type, const psatd_plan_s* plan, const std::vector<i
   return ps;
 }
 
-// Wave-resident fused z pass: 2D (wave2d.hip) in the vacuum forms, 3D
-// (wave3d.hip) in the PSATD forms; FP32 storage, every z length compiled.
-bool wave_z_eligible(const psatd_plan_s* plan) {
+// The fused z pass with compile-time lengths (zfused.hpp) takes the plan if
+// every z length is compiled for its form.  Grids of at most 4 columns (nx <= 8)
+// with 2D lines of 1024 points and more keep the generic kernel: they are not
+// physical runs but what exercises its modes-per-thread fallbacks for long
+// lines (it is the slower one there too: 43 against 26 us at 1024 points with
+// sources, 145 against 40 at 4096).
+constexpr int kFewColumns = 5;
+bool fixed_z_eligible(const psatd_plan_s* plan) {
   const psatd_config& c = plan->cfg;
-  if (c.flags & PSATD_FLAG_GENERIC_KERNELS) return false;
-  if (c.precision != PSATD_FP32 || c.path != PSATD_PATH_FUSED) return false;
-  if (plan->ndim == 2) {
-    if (plan->src_form != kVacuum && plan->src_form != kPstdVacuum) return false;
-    for (const PatchDev& P : plan->host_patches)
-      if (!wave2d::z_supported(P.nz)) return false;
-    return true;
+  if ((c.flags & PSATD_FLAG_GENERIC_KERNELS) || c.path != PSATD_PATH_FUSED) return false;
+  for (const PatchDev& P : plan->host_patches) {
+    if (!zfused::supported(c.precision, plan->ndim, plan->src_form, P.nz)) return false;
+    if (plan->ndim == 2 && P.nz >= 1024 && P.mx < kFewColumns) return false;
   }
-  if (src_is_pstd(plan->src_form)) return false;
-  for (const PatchDev& P : plan->host_patches)
-    if (!wave2d::z3_supported(P.nz)) return false;
   return true;
 }
 
-// One work item per wavefront: the z lines (kx columns) one wave holds.  In
-// 2D, one launch per z length: lengths at 8 points per lane run one set per
-// wavefront (two wavefronts per item), the others both sets.
-Pass make_wave_z_pass(const psatd_plan_s* plan, std::vector<WorkItem>& items) {
+// Work items of up to zfused::lines_per_item() z lines, one launch per length.
+Pass make_fixed_z_pass(const psatd_plan_s* plan, std::vector<WorkItem>& items) {
   Pass ps;
   ps.type = kWaveZ;
   ps.name = "z_fused";
   const size_t first = items.size();
   double bytes = 0.0;
-  if (plan->ndim == 2) {
-    std::set<int> lengths;
-    for (const PatchDev& P : plan->host_patches) lengths.insert(P.nz);
-    size_t lds = 0;
-    for (int L : lengths) {
-      SubLaunch sub;
-      sub.L = L;
-      sub.first = static_cast<int>(items.size() - first);
-      const int G = wave2d::z_lines_per_item(L);
-      for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
-        const PatchDev& P = plan->host_patches[pi];
-        if (P.nz != L) continue;
-        const int nlines = P.mx * P.ny;
-        for (int l = 0; l < nlines; l += G)
-          items.push_back(WorkItem{static_cast<int>(pi), l, std::min(G, nlines - l), -1});
-        const double cells = static_cast<double>(P.nx) * P.ny * P.nz;
-        bytes += (plan->nin + 6) * cells * plan->elem;
-      }
-      sub.nitems = static_cast<int>(items.size() - first) - sub.first;
-      sub.region = wave2d::z_region(L);
-      const int waves = wave2d::z_set_supported(L) ? 2 * sub.nitems : sub.nitems;
-      sub.full = (waves + wave2d::kWavesPerBlock - 1) / wave2d::kWavesPerBlock;
-      const size_t sub_lds = static_cast<size_t>(sub.region) * wave2d::kWavesPerBlock * sizeof(double2);
-      sub.shape = LaunchShape{sub.full, wave2d::kBlock, sub_lds};
-      lds = std::max(lds, sub_lds);
-      ps.region = std::max(ps.region, sub.region);
-      ps.lines = std::max(ps.lines, G);
-      ps.subs.push_back(sub);
+  std::set<int> lengths;
+  for (const PatchDev& P : plan->host_patches) lengths.insert(P.nz);
+  size_t lds = 0;
+  int block = 64, total = 0;
+  for (int L : lengths) {
+    SubLaunch sub;
+    sub.L = L;
+    sub.first = static_cast<int>(items.size() - first);
+    const int T = zfused::lines_per_item(L);
+    for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
+      const PatchDev& P = plan->host_patches[pi];
+      if (P.nz != L) continue;
+      const int nlines = P.mx * P.ny;
+      for (int l = 0; l < nlines; l += T)
+        items.push_back(WorkItem{static_cast<int>(pi), l, std::min(T, nlines - l), -1});
+      const double cells = static_cast<double>(P.nx) * P.ny * P.nz;
+      bytes += (plan->nin + 6) * cells * plan->elem;
     }
-    ps.nitems = static_cast<int>(items.size() - first);
-    int total = 0;
-    for (const SubLaunch& sub : ps.subs) total += sub.shape.grid;
-    ps.shape = LaunchShape{total, wave2d::kBlock, lds};
-    ps.bytes = bytes;
-    ps.d_items = reinterpret_cast<WorkItem*>(first);
-    return ps;
-  }
-  for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
-    const PatchDev& P = plan->host_patches[pi];
-    const int G = wave2d::z_lines_per_item(P.nz);
-    const int nlines = P.mx * P.ny;
-    for (int l = 0; l < nlines; l += G)
-      items.push_back(WorkItem{static_cast<int>(pi), l, std::min(G, nlines - l), -1});
-    ps.region = std::max(ps.region, P.ndim == 2 ? wave2d::z_region(P.nz) : wave2d::z3_region(P.nz));
-    ps.lines = std::max(ps.lines, G);
-    const double cells = static_cast<double>(P.nx) * P.ny * P.nz;
-    bytes += (plan->nin + 6) * cells * plan->elem;
+    sub.nitems = static_cast<int>(items.size() - first) - sub.first;
+    sub.full = zfused::workgroups(plan->ndim, sub.nitems);
+    const size_t sub_lds = zfused::lds_bytes(plan->cfg.precision, plan->ndim, plan->src_form, L);
+    sub.shape = LaunchShape{sub.full, zfused::block(L), sub_lds};
+    lds = std::max(lds, sub_lds);
+    block = std::max(block, sub.shape.block);
+    total += sub.full;
+    ps.lines = std::max(ps.lines, T);
+    ps.subs.push_back(sub);
   }
   ps.nitems = static_cast<int>(items.size() - first);
-  const int blocks = (ps.nitems + wave2d::kWavesPerBlock - 1) / wave2d::kWavesPerBlock;
-  ps.shape = LaunchShape{blocks, wave2d::kBlock,
-                         static_cast<size_t>(ps.region) * wave2d::kWavesPerBlock * sizeof(double2)};
+  ps.shape = LaunchShape{total, block, lds};
   ps.bytes = bytes;
   ps.d_items = reinterpret_cast<WorkItem*>(first);
   return ps;
@@ -975,18 +934,10 @@ psatd_status enqueue_pass(const psatd_plan_s* plan, const Pass& ps, const FieldP
       });
       break;
     case kWaveZ:
-      if (plan->ndim == 2) {
-        e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
-          return wave2d::z_set_supported(sub.L)
-                     ? wave2d::launch_z_set(plan->src_form, sub.L, sub.shape, t, plan->d_patches,
-                                            ps.d_items + sub.first, sub.nitems, ws, ph, sub.region)
-                     : wave2d::launch_z_fused(plan->src_form, sub.shape, t, plan->d_patches,
-                                              ps.d_items + sub.first, sub.nitems, ws, ph, sub.region);
-        });
-      } else {
-        e = wave2d::launch_z3_fused(plan->src_form, ps.shape, s, plan->d_patches, ps.d_items,
-                                    ps.nitems, ws, ph, ps.region);
-      }
+      e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
+        return zfused::launch(plan->cfg.precision, plan->ndim, plan->src_form, sub.L, sub.shape.grid,
+                              t, plan->d_patches, ps.d_items + sub.first, sub.nitems, ws, ph);
+      });
       break;
     case kFastXFwd:
       e = fast2d::launch_x_fwd(ps.shape, s, plan->d_patches, ps.d_items, ps.nitems, f, ws);
@@ -1171,7 +1122,8 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
   // (line passes: also at both radix schedules, radix-4 stages at 4 points
   // per thread and radices up to 8 at 8; they round differently, and each
   // is checked against the oracle by the tests)
-  // (the wave-resident z pass: also the generic fused pass, at every choice)
+  // (the z pass with compile-time lengths: also the generic fused pass, at
+  // every choice)
   // (line passes: also the kernels with compile-time lengths where they apply)
   const bool linelike = ps.type == kLine || ps.type == kWaveX;
   std::vector<int> vars = {0};
@@ -1207,13 +1159,12 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
   return cands;
 }
 
-// The launch grids a candidate is timed at: one workgroup per item (the wave
-// z pass: one wavefront per item), or a persistent grid of k workgroups per
+// The launch grids a candidate is timed at: one workgroup per item, or a persistent grid of k workgroups per
 // CU; per-length launches take a code (0: every item its own workgroup, k: k
 // per CU) that set_grid turns into each launch's grid.
 std::vector<int> grid_choices(const psatd_plan_s* plan, const Pass& c) {
   if (!c.subs.empty()) return {0, 1, 2, 4, 8};
-  const int full = c.type == kWaveZ ? c.shape.grid : c.nitems;
+  const int full = c.nitems;
   std::vector<int> grids = {full};
   for (int k : {1, 2, 4, 8})
     if (k * plan->num_cus < full) grids.push_back(k * plan->num_cus);
@@ -1281,6 +1232,19 @@ bool earlier_fixed_line_choice(const psatd_plan_s* plan, const Pass& c, const Ch
   return false;
 }
 
+// The same for the z pass: one wave of 64 / S lines per item, FP32, up to 512
+// points (3D: only powers of two).
+bool earlier_fixed_z_choice(const psatd_plan_s* plan, const Choice& ch) {
+  if (ch.type != kWaveZ || ch.ct != 0 || ch.mpt != 0 || ch.ppt != 0) return false;
+  if (plan->cfg.precision != PSATD_FP32) return false;
+  int rows = 0;
+  for (const PatchDev& P : plan->host_patches) {
+    if (P.nz > 512 || (P.nz % 3 != 0 && (P.nz & (P.nz - 1)) != 0)) return false;
+    rows = std::max(rows, 64 * (P.nz % 3 == 0 ? 12 : 8) / P.nz);
+  }
+  return ch.lines == rows;
+}
+
 // Apply the choices of a tuning string (from psatd_plan_tuning of a plan with
 // the same configuration and patches): no timing launch.
 psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice) {
@@ -1297,7 +1261,8 @@ psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice)
       const Pass& c = cands[ci].pass;
       if ((c.type == ch.type && ch.ct == 0 && c.lines == ch.lines && c.mpt == ch.mpt &&
            c.ppt == ch.ppt) ||
-          (c.type == kWaveX && earlier_fixed_line_choice(plan, c, ch)))
+          (c.type == kWaveX && earlier_fixed_line_choice(plan, c, ch)) ||
+          (c.type == kWaveZ && earlier_fixed_z_choice(plan, ch)))
         pick = static_cast<int>(ci);
     }
     if (pick < 0)
@@ -1602,8 +1567,8 @@ psatd_status build_plan(psatd_plan_s* plan) {
     };
     plan->passes.push_back(line(kXFwd, in_comps));
   if (plan->ndim == 3) plan->passes.push_back(line(kYFwd, in_comps));
-  if (cfg.path == PSATD_PATH_FUSED && wave_z_eligible(plan)) {
-    plan->passes.push_back(make_wave_z_pass(plan, items));
+  if (fixed_z_eligible(plan)) {
+    plan->passes.push_back(make_fixed_z_pass(plan, items));
   } else if (cfg.path == PSATD_PATH_FUSED && fused_fits(plan, items)) {
     Pass fz;
     psatd_status st = make_fused_pass(plan, items, &fz);
@@ -1699,8 +1664,6 @@ psatd_status create_plan(const psatd_config* cfg, const psatd_patch_desc* patche
       if (!configured.count(device)) {
         hipError_t e = configure_kernel_attributes();
         if (e == hipSuccess) e = fast2d::configure_attributes();
-        if (e == hipSuccess) e = wave2d::configure_attributes();
-        if (e == hipSuccess) e = wave2d::configure_z3_attributes();
         if (e != hipSuccess) return hip_fail(e, "kernel attributes");
         if (lookup_scratch(device) != PSATD_OK)
           return fail(PSATD_ERR_HIP, "hipGetSymbolAddress(scratch) failed");

@@ -225,23 +225,25 @@ struct Radices {
   int P, n, r[5];
 };
 
-// Schedules of the passes that hold one transform at a time.
-// Every radix divides P; the first radix divides S = L / P or is a multiple of
-// it, so that the padded exchange addresses are a thread base plus constants.
+// Schedules of the passes that hold one transform at a time.  Every radix
+// divides P.  The last stage has P / R twiddle bases per thread: up to three of
+// them are cheaper than a twiddled butterfly of 24 (154 registers against 218
+// at 192 = 24.8); from four on the last radix is P (1152 = 24.2.24 holds 2
+// bases, 24.24.2 would hold 13).
 constexpr Radices line_radices(int L) {
   switch (L) {
-    case 16: return {8, 2, {8, 2}};
+    case 16: return {8, 2, {2, 8}};
     case 18: return {18, 1, {18}};
-    case 24: return {12, 2, {12, 2}};
-    case 32: return {8, 2, {8, 4}};
-    case 36: return {12, 2, {12, 3}};
-    case 48: return {12, 2, {12, 4}};
+    case 24: return {12, 2, {2, 12}};
+    case 32: return {8, 2, {4, 8}};
+    case 36: return {12, 2, {3, 12}};
+    case 48: return {12, 2, {4, 12}};
     case 54: return {18, 2, {18, 3}};
     case 64: return {8, 2, {8, 8}};
     case 72: return {12, 2, {12, 6}};
     case 96: return {24, 2, {12, 8}};
     case 108: return {18, 2, {18, 6}};
-    case 128: return {16, 2, {16, 8}};
+    case 128: return {16, 2, {8, 16}};
     case 144: return {12, 2, {12, 12}};
     case 162: return {18, 2, {18, 9}};
     case 192: return {24, 2, {24, 8}};
@@ -250,59 +252,58 @@ constexpr Radices line_radices(int L) {
     case 288: return {24, 2, {24, 12}};
     case 324: return {18, 2, {18, 18}};
     case 384: return {24, 3, {8, 8, 6}};
-    case 432: return {12, 3, {12, 12, 3}};
-    case 486: return {18, 3, {9, 18, 3}};
+    case 432: return {12, 3, {12, 3, 12}};
+    case 486: return {18, 3, {9, 3, 18}};
     case 512: return {8, 3, {8, 8, 8}};
     case 576: return {24, 2, {24, 24}};
-    case 648: return {18, 3, {18, 18, 2}};
+    case 648: return {18, 3, {18, 2, 18}};
     case 768: return {24, 3, {8, 8, 12}};
-    case 864: return {24, 3, {12, 24, 3}};
-    case 972: return {18, 3, {18, 18, 3}};
-    case 1024: return {16, 3, {16, 16, 4}};
-    case 1152: return {24, 3, {24, 24, 2}};
-    case 1296: return {12, 4, {12, 12, 3, 3}};
-    case 1458: return {18, 3, {9, 18, 9}};
+    case 864: return {24, 3, {12, 3, 24}};
+    case 1024: return {16, 3, {16, 4, 16}};
+    case 1152: return {24, 3, {24, 2, 24}};
+    case 1296: return {12, 4, {12, 3, 3, 12}};
     case 1536: return {24, 3, {8, 8, 24}};
-    case 1728: return {24, 3, {24, 24, 3}};
-    case 2048: return {16, 3, {16, 16, 8}};
+    case 1728: return {24, 3, {24, 3, 24}};
+    case 2048: return {16, 3, {16, 8, 16}};
     default: return {0, 0, {0}};
   }
 }
 
 // Schedules of the fused z passes, whose threads also hold a set of
-// transformed inputs: at most 12 points per thread.
+// transformed inputs: at most 12 points per thread, and one twiddle base per
+// stage (the last radix is P).
 constexpr Radices fused_radices(int L) {
   switch (L) {
-    case 32: return {8, 2, {8, 4}};
-    case 36: return {12, 2, {12, 3}};
-    case 48: return {12, 2, {12, 4}};
-    case 54: return {6, 3, {6, 3, 3}};
+    case 32: return {8, 2, {4, 8}};
+    case 36: return {12, 2, {3, 12}};
+    case 48: return {12, 2, {4, 12}};
+    case 54: return {6, 3, {3, 3, 6}};
     case 64: return {8, 2, {8, 8}};
-    case 72: return {12, 2, {12, 6}};
-    case 96: return {12, 3, {4, 12, 2}};
-    case 108: return {12, 3, {3, 12, 3}};
-    case 128: return {8, 3, {8, 4, 4}};
+    case 72: return {12, 2, {6, 12}};
+    case 96: return {12, 3, {4, 2, 12}};
+    case 108: return {12, 3, {3, 3, 12}};
+    case 128: return {8, 3, {8, 2, 8}};
     case 144: return {12, 2, {12, 12}};
-    case 162: return {6, 4, {6, 3, 3, 3}};
-    case 192: return {12, 3, {4, 12, 4}};
-    case 216: return {12, 3, {6, 12, 3}};
-    case 256: return {8, 3, {8, 8, 4}};
-    case 288: return {12, 3, {12, 12, 2}};
-    case 324: return {6, 4, {6, 6, 3, 3}};
-    case 384: return {12, 4, {4, 4, 4, 6}};
-    case 432: return {12, 3, {12, 12, 3}};
+    case 162: return {6, 4, {3, 3, 3, 6}};
+    case 192: return {12, 3, {4, 4, 12}};
+    case 216: return {12, 3, {6, 3, 12}};
+    case 256: return {8, 3, {8, 4, 8}};
+    case 288: return {12, 3, {12, 2, 12}};
+    case 324: return {6, 4, {6, 3, 3, 6}};
+    case 384: return {12, 4, {4, 4, 2, 12}};
+    case 432: return {12, 3, {12, 3, 12}};
     case 512: return {8, 3, {8, 8, 8}};
-    case 576: return {12, 3, {12, 12, 4}};
-    case 648: return {12, 4, {6, 12, 3, 3}};
+    case 576: return {12, 3, {12, 4, 12}};
+    case 648: return {12, 4, {6, 3, 3, 12}};
     case 768: return {12, 4, {4, 4, 4, 12}};
-    case 864: return {12, 3, {12, 12, 6}};
-    case 1024: return {8, 4, {8, 8, 4, 4}};
-    case 1152: return {12, 4, {12, 12, 4, 2}};
-    case 1296: return {12, 4, {12, 12, 3, 3}};
-    case 1536: return {12, 5, {4, 4, 6, 4, 4}};
+    case 864: return {12, 3, {12, 6, 12}};
+    case 1024: return {8, 4, {8, 8, 2, 8}};
+    case 1152: return {12, 4, {12, 4, 2, 12}};
+    case 1296: return {12, 4, {12, 3, 3, 12}};
+    case 1536: return {12, 5, {4, 4, 2, 4, 12}};
     case 1728: return {12, 3, {12, 12, 12}};
-    case 2048: return {8, 4, {8, 8, 8, 4}};
-    case 2304: return {12, 4, {12, 12, 4, 4}};
+    case 2048: return {8, 4, {8, 8, 4, 8}};
+    case 2304: return {12, 4, {12, 4, 4, 12}};
     case 3072: return {12, 5, {4, 4, 4, 4, 12}};
     case 4096: return {8, 4, {8, 8, 8, 8}};
     default: return {0, 0, {0}};
@@ -407,6 +408,11 @@ PSATD_HD void stage(double2 (&v)[SC::P], const Base<SC, I>& tb) {
     for (int q = 0; q < R; ++q) a[q] = v[t + q * BPT];
     if constexpr (SC::ns(I) > 1) {
       double2 u = tb.w[t % bases<SC, I>()];
+#if defined(__HIP_DEVICE_COMPILE__)
+      // a copy the optimizer cannot see through: the powers of the base are
+      // formed in each transform, not kept live from one to the next
+      asm volatile("" : "+v"(u.x), "+v"(u.y));
+#endif
       if constexpr (SIGN > 0) u.y = -u.y;
       dft<R, SIGN, true>(a, u);
     } else {

@@ -18,6 +18,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "fft.hpp"
 #include "internal.hpp"
 
@@ -88,13 +90,39 @@ __host__ __device__ inline void psatd_sincos(double h, double* s_out, double* c_
   *c_out = ((quad + 1) & 2) ? -cv : cv;
 }
 
-__host__ __device__ inline Coef psatd_coef(double K, double dt, double c, double eps0,
+// sqrt(x) and 1 / sqrt(x) (0 and 0 at x = 0) from one reciprocal square root:
+// a coupled Newton iteration from the hardware estimate (2^-24 relative), then
+// the residual of each result, which leaves both within one unit of the last
+// place.  A correctly rounded square root and a division take 26 instructions
+// per mode instead of these 12.
+__host__ __device__ inline void psatd_roots(double x, double* root, double* inverse) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  g = fma(fma(-g, g, x), h, g);
+  double r = h + h;
+  r = fma(fma(-g, r, 1.0), r, r);
+#else
+  const double g = std::sqrt(x), r = 1.0 / g;
+#endif
+  *root = x > 0.0 ? g : x;  // (a NaN stays one)
+  *inverse = x > 0.0 ? r : 0.0;
+}
+
+// The coefficients of a mode with wavenumber squared K2.
+__host__ __device__ inline Coef psatd_coef(double K2, double dt, double c, double eps0,
                                            double scale) {
-  const double th = c * K * dt;
-  const double h = 0.5 * th;
+  double K, rK;
+  psatd_roots(K2, &K, &rK);
+  const double half = 0.5 * c * dt;  // theta / 2 = half K
+  const double h = half * K;
+  const double th = 2.0 * h;
   double sh, ch;
   psatd_sincos(h, &sh, &ch);
-  const double ih = (h > 0.0) ? 1.0 / h : 0.0;
+  const double ih = rK * (1.0 / half);
   const double sinc_h = (h > 0.0) ? sh * ih : 1.0;
   const double sinc_th = sinc_h * ch;  // sin(th)/th = (2 sh ch)/(2 h)
   // Both forms are evaluated and one is selected: no divergent branch.
@@ -154,7 +182,7 @@ __device__ __forceinline__ void update_mode(const double kx, const double ky, co
         csub(cscale(J[2], ky), cscale(J[1], kz)),
         csub(cscale(J[0], kz), cscale(J[2], kx)),
         csub(cscale(J[1], kx), cscale(J[0], ky))};
-    const double sj = q.S / eps0;
+    const double sj = q.Se;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       Eo[i] = csub(Eo[i], cscale(J[i], sj));
@@ -219,6 +247,87 @@ __device__ __forceinline__ void pstd_update_mode(const double kx, const double k
 //                  = eps0 c^2 X1 k (k.E) - dt X2 k (k.J)                 (J form)
 // These are the general update with k_y = 0 written out, so that no term is
 // multiplied by an explicit zero.
+
+// a + i s b and a - i s b for real s
+__device__ __forceinline__ double2 add_i(double2 a, double s, double2 b) {
+  return make_double2(fma(-s, b.y, a.x), fma(s, b.x, a.y));
+}
+__device__ __forceinline__ double2 sub_i(double2 a, double s, double2 b) {
+  return make_double2(fma(s, b.y, a.x), fma(-s, b.x, a.y));
+}
+__device__ __forceinline__ double2 add_r(double2 a, double s, double2 b) {
+  return make_double2(fma(s, b.x, a.x), fma(s, b.y, a.y));
+}
+
+// Advance one polarization set of one mode, in the component order of
+// Group<G, SRC>: in holds the set's inputs, the first three become the outputs.
+// `scale` is the 1/N of the inverse FFTs.
+template <int G, int SRC>
+__device__ __forceinline__ void update_set(double kx, double kz, double dt, double c, double eps0,
+                                           double scale, double2* in) {
+  if constexpr (src_is_pstd(SRC)) {
+    const double cdt = c * c * dt;
+    if constexpr (G == 0) {
+      const double2 bx = add_i(in[1], dt * kz, in[0]), bz = sub_i(in[2], dt * kx, in[0]);
+      double2 e = sub_i(add_i(in[0], cdt * kz, bx), cdt * kx, bz);
+      if constexpr (SRC == kPstdJ) e = add_r(e, -dt / eps0, in[3]);
+      in[0] = cscale(e, scale);
+      in[1] = cscale(bx, scale);
+      in[2] = cscale(bz, scale);
+    } else {
+      const double2 by = add_i(sub_i(in[2], dt * kz, in[0]), dt * kx, in[1]);
+      double2 ex = sub_i(in[0], cdt * kz, by), ez = add_i(in[1], cdt * kx, by);
+      if constexpr (SRC == kPstdJ) {
+        ex = add_r(ex, -dt / eps0, in[3]);
+        ez = add_r(ez, -dt / eps0, in[4]);
+      }
+      in[0] = cscale(ex, scale);
+      in[1] = cscale(ez, scale);
+      in[2] = cscale(by, scale);
+    }
+  } else {
+    const Coef q = psatd_coef(kx * kx + kz * kz, dt, c, eps0, scale);
+    const double cS = c * c * q.S;
+    if constexpr (G == 0) {
+      double2 e = cscale(in[0], q.C), bx = cscale(in[1], q.C), bz = cscale(in[2], q.C);
+      e = sub_i(add_i(e, cS * kz, in[1]), cS * kx, in[2]);
+      bx = add_i(bx, q.S * kz, in[0]);
+      bz = sub_i(bz, q.S * kx, in[0]);
+      if constexpr (SRC != kVacuum) {
+        e = add_r(e, -q.Se, in[3]);
+        bx = sub_i(bx, q.X1 * kz, in[3]);
+        bz = add_i(bz, q.X1 * kx, in[3]);
+      }
+      in[0] = e;
+      in[1] = bx;
+      in[2] = bz;
+    } else {
+      double2 ex = sub_i(cscale(in[0], q.C), cS * kz, in[2]);
+      double2 ez = add_i(cscale(in[1], q.C), cS * kx, in[2]);
+      double2 by = add_i(sub_i(cscale(in[2], q.C), q.S * kz, in[0]), q.S * kx, in[1]);
+      if constexpr (SRC != kVacuum) {
+        ex = add_r(ex, -q.Se, in[3]);
+        ez = add_r(ez, -q.Se, in[4]);
+        by = sub_i(add_i(by, q.X1 * kz, in[3]), q.X1 * kx, in[4]);
+        if constexpr (SRC == kJForm) {
+          const double a = eps0 * c * c * q.X1, b = dt * q.X2;
+          const double2 kE = add_r(cscale(in[0], kx), kz, in[1]);
+          const double2 kJ = add_r(cscale(in[3], kx), kz, in[4]);
+          const double2 l = add_r(cscale(kE, a), -b, kJ);
+          ex = add_r(ex, kx, l);
+          ez = add_r(ez, kz, l);
+        } else {
+          const double2 lam = add_r(cscale(in[5], q.X3), -q.X2, in[6]);
+          ex = add_i(ex, kx, lam);
+          ez = add_i(ez, kz, lam);
+        }
+      }
+      in[0] = ex;
+      in[1] = ez;
+      in[2] = by;
+    }
+  }
+}
 
 // FP32 storage <-> FP64 arithmetic.
 __device__ __forceinline__ double2 ld2(const float2& v) { return make_double2(v.x, v.y); }

@@ -1,0 +1,79 @@
+"""The fused z pass with compile-time lengths against the oracle: every compiled
+length in 2D (all forms, both precisions, PSTD) and 3D, with line counts that
+leave a short last item.
+
+Tolerances are the parity ones (see test_gpu_lines.py): FP64 1e-12, FP32 1e-5."""
+
+import numpy as np
+import pytest
+
+import fixtures
+import oracle.contrast
+import paper_1608_05739_amd as pk
+from gpu_support import compare, fields_to_device, from_device, run_gpu, run_oracle, say, to_device
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "fp32": 1e-5}
+LENGTHS_3D = [32, 36, 48, 54, 64, 72, 96, 108, 128, 144, 162, 192, 216, 256, 288, 324, 384, 432, 512]
+LENGTHS_2D = LENGTHS_3D + [576, 648, 768, 864, 1024, 1152, 1296, 1536, 1728, 2048, 2304, 3072, 4096]
+
+
+def _check(index, shape, precision, form):
+    if form == "vacuum":
+        w = fixtures.workload(index, shape=shape, steps=2)
+        w.sources = False
+    else:
+        w = fixtures.workload(index, shape=shape, steps=2)
+    mode = {"rho": "rho", "J": "j", "vacuum": "vacuum"}[form]
+    plan = pk.Plan(w.patches, precision=precision, source_mode=mode, path="fused")
+    info = plan.info
+    plan.close()
+    line = [ln for ln in info.splitlines() if ln.strip().startswith("z_fused")][0]
+    assert line.endswith("kernel=wave" if precision == "fp32" else "kernel=compile-time"), info
+    say(f"fixed z {shape} {precision} {form}")
+    f = form if form != "vacuum" else "rho"
+    err = compare(run_gpu(w, precision, "fused", w.steps, form=f), run_oracle(w, precision, w.steps, form=f),
+                  precision=precision)
+    assert err < TOL[precision]
+
+
+@pytest.mark.parametrize("L", LENGTHS_2D)
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_2d_every_z_length_and_form(L, precision):
+    if precision == "fp64" and L > 2048:
+        pytest.skip("FP64 plans run the plain z passes above 2048 points")
+    for form in ("rho", "J", "vacuum"):
+        _check(1, (L, 54), precision, form)  # 27 columns
+
+
+@pytest.mark.parametrize("L", LENGTHS_3D)
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_3d_every_z_length_and_form(L, precision):
+    for form in ("rho", "J", "vacuum"):
+        if precision == "fp64" and form == "rho" and L % 3 == 0 and L not in (54, 162, 324):
+            continue  # generic kernel
+        _check(2, (L, 6, 6), precision, form)  # 18 lines
+
+
+@pytest.mark.parametrize("L", [64, 96, 162, 1024, 2304])
+@pytest.mark.parametrize("mode", ["vacuum", "j"])
+def test_pstd_sets(L, mode):
+    import torch
+    w = fixtures.workload(1, shape=(L, 48), steps=2)
+    p = w.patches[0]
+    p.dt *= 0.4
+    plan = pk.Plan([p], precision="fp32", source_mode=mode, pstd=True)
+    assert "kernel=wave" in [ln for ln in plan.info.splitlines() if "z_fused" in ln][0]
+    E, B = fields_to_device(w.E0, plan, "fp32"), fields_to_device(w.B0, plan, "fp32")
+    r32 = lambda v: [np.asarray(a, np.float32).astype(np.float64) for a in v]  # noqa: E731
+    J = r32(w.schedule[0].sources(0)[0]) if mode == "j" else None
+    Eo, Bo = oracle.contrast.pstd_step(r32(w.E0[0]), r32(w.B0[0]), J, d=p.d, dt=p.dt)
+    plan.push(E, B, [to_device([j], plan, "fp32") for j in J] if J else None)
+    torch.cuda.synchronize()
+    got = [from_device(t, plan)[0] for t in E + B]
+    plan.close()
+    ref = list(Eo) + list(Bo)
+    err = np.sqrt(sum(np.sum((g - r) ** 2) for g, r in zip(got, ref)) / sum(np.sum(r * r) for r in ref))
+    say(f"pstd sets {L} {mode}: {err:.1e}")
+    assert err < TOL["fp32"]
