@@ -91,7 +91,7 @@ PSATD_HD double2 sqr(double2 a) {
 // a * exp(SIGN 2 pi i M / N)
 template <int N, int M, int SIGN>
 PSATD_HD double2 rot(double2 a) {
-  constexpr int m = 144 / N * M;
+  constexpr int m = 144 / N * M % 144;
   static_assert(144 % N == 0 && cos_72(m) <= 1.0, "constant twiddle");
   if constexpr (M == 0) {
     return a;
@@ -129,6 +129,31 @@ PSATD_HD void bfly1_i(double2& a, double2& b) {
   b = t;
 }
 
+// The powers of a twiddle base that a butterfly of radix R uses: 1 and twice
+// those of R / 2; 1, 2 for R = 3; 1, 2 and three times those of 3 for R = 9.
+constexpr int power_count(int R) { return R == 1 ? 0 : (R == 3 ? 2 : (R == 9 ? 4 : 1 + power_count(R / 2))); }
+constexpr int power(int R, int j) {
+  if (R % 2 == 0) return j == 0 ? 1 : 2 * power(R / 2, j - 1);
+  return j < 2 ? j + 1 : 3 * (j - 1);
+}
+// The same from the base alone.  Each squaring doubles the relative error of
+// the table's rounding, which FP32 storage does not show (2^-24); FP64 storage
+// takes the powers from the table (a 1024-point transform is then off by
+// 2.6e-16 instead of 4.0e-16).
+template <int R>
+PSATD_HD void powers(double2 u, double2* p) {
+  if constexpr (R == 1) {
+    return;
+  } else if constexpr (R % 2 == 0) {
+    p[0] = u;
+    if constexpr (R > 2) powers<R / 2>(sqr(u), p + 1);
+  } else {
+    p[0] = u;
+    p[1] = sqr(u);
+    if constexpr (R == 9) powers<3>(mul(p[1], u), p + 2);
+  }
+}
+
 // x0, x1, x2 <- DFT of length 3 of (x0, u x1, u^2 x2) (T) or (x0, x1, x2)
 template <int SIGN, bool T>
 PSATD_HD void dft3(double2& x0, double2& x1, double2& x2, double2 u, double2 u2) {
@@ -149,34 +174,32 @@ PSATD_HD void dft3(double2& x0, double2& x1, double2& x2, double2 u, double2 u2)
 }
 
 // In-place DFT of length R (natural order in and out) of a[q] u^q (T) or a[q]:
-// v[k] <- sum_q a[q] u^q exp(SIGN 2 pi i q k / R).  Decimation in time: the
-// halves (or thirds) are transforms with base u^2 (u^3), joined by butterflies
-// with the twiddles u W_R^k.
+// v[k] <- sum_q a[q] u^q exp(SIGN 2 pi i q k / R), p the powers of u.
+// Decimation in time: the halves (or thirds) are transforms with base u^2
+// (u^3), joined by butterflies with the twiddles u W_R^k.
 template <int R, int SIGN, bool T>
-PSATD_HD void dft(double2 (&a)[R], double2 u) {
+PSATD_HD void dft(double2 (&a)[R], const double2* p) {
   if constexpr (R == 1) {
     return;
   } else if constexpr (R == 3) {
-    dft3<SIGN, T>(a[0], a[1], a[2], u, T ? sqr(u) : u);
+    dft3<SIGN, T>(a[0], a[1], a[2], p[0], p[1]);
   } else if constexpr (R % 2 == 1) {
     static_assert(R == 9, "odd radix");
     double2 y[3][3];
-    double2 u3 = u;
-    if constexpr (T) u3 = mul(sqr(u), u);
     static_for<0, 3>([&](auto rc) __attribute__((always_inline)) {
       constexpr int r = decltype(rc)::value;
       for (int q = 0; q < 3; ++q) y[r][q] = a[r + 3 * q];
-      dft<3, SIGN, T>(y[r], u3);
+      dft<3, SIGN, T>(y[r], p + 2);
     });
     static_for<0, 3>([&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value;
       if constexpr (!T && k == 0) {
-        dft3<SIGN, false>(y[0][0], y[1][0], y[2][0], u, u);
+        dft3<SIGN, false>(y[0][0], y[1][0], y[2][0], p[0], p[1]);
       } else {
         constexpr double cs = cos_72(16 * k), sn = SIGN * sin_72(16 * k);
-        const double2 w = T ? rot<9, k, SIGN>(u) : c2(cs, sn);
         constexpr double cs2 = cos_72(32 * k), sn2 = SIGN * sin_72(32 * k);
-        const double2 w2 = T ? sqr(w) : c2(cs2, sn2);
+        const double2 w = T ? rot<9, k, SIGN>(p[0]) : c2(cs, sn);
+        const double2 w2 = T ? rot<9, 2 * k, SIGN>(p[1]) : c2(cs2, sn2);
         dft3<SIGN, true>(y[0][k], y[1][k], y[2][k], w, w2);
       }
     });
@@ -190,16 +213,14 @@ PSATD_HD void dft(double2 (&a)[R], double2 u) {
       e[q] = a[2 * q];
       o[q] = a[2 * q + 1];
     }
-    double2 u2 = u;
-    if constexpr (T && H > 1) u2 = sqr(u);
-    dft<H, SIGN, T>(e, u2);
-    dft<H, SIGN, T>(o, u2);
+    dft<H, SIGN, T>(e, p + 1);
+    dft<H, SIGN, T>(o, p + 1);
     // twiddles u W_R^k; from k = R / 4 on they repeat with a factor SIGN i
     constexpr int K = R % 4 == 0 ? R / 4 : H;
     static_for<0, K>([&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value;
       if constexpr (T) {
-        const double2 w = rot<R, k, SIGN>(u);
+        const double2 w = rot<R, k, SIGN>(p[0]);
         bfly(e[k], o[k], w);
         if constexpr (K < H) bfly_i<SIGN>(e[k + K], o[k + K], w);
       } else if constexpr (k == 0) {
@@ -387,36 +408,51 @@ constexpr int bases() {
   if (ns % SC::S == 0) return ns / SC::S < bpt ? ns / SC::S : bpt;
   return bpt;
 }
-template <typename SC, int I>
+// What a thread keeps of them: the base alone, or (TABLE) its powers too.
+template <typename SC, int I, bool TABLE>
 struct Base {
-  double2 w[bases<SC, I>() > 0 ? bases<SC, I>() : 1];
+  static constexpr int kPow = TABLE ? power_count(SC::radix(I)) : 1;
+  static constexpr int kBases = bases<SC, I>() > 0 ? bases<SC, I>() : 1;
+  double2 w[kBases][kPow > 0 ? kPow : 1];
   PSATD_HD void load(const double2* tw, int s) {
 #pragma unroll
-    for (int t = 0; t < bases<SC, I>(); ++t) w[t] = gload(tw, twiddle_index<SC, I>(s, t));
+    for (int t = 0; t < bases<SC, I>(); ++t) {
+      const int i = twiddle_index<SC, I>(s, t);
+      static_for<0, kPow>([&](auto jc) __attribute__((always_inline)) {
+        constexpr int e = TABLE ? power(SC::radix(I), decltype(jc)::value) : 1;
+        w[t][decltype(jc)::value] = gload(tw, i * e);
+      });
+    }
   }
 };
 
 // Stage I on the thread's points: v[t + q P/R] is input q of butterfly t, and
 // output q after it.
-template <typename SC, int I, int SIGN>
-PSATD_HD void stage(double2 (&v)[SC::P], const Base<SC, I>& tb) {
-  constexpr int R = SC::radix(I), BPT = SC::P / R;
+template <typename SC, int I, int SIGN, bool TABLE>
+PSATD_HD void stage(double2 (&v)[SC::P], const Base<SC, I, TABLE>& tb) {
+  constexpr int R = SC::radix(I), BPT = SC::P / R, NPOW = power_count(R);
 #pragma unroll
   for (int t = 0; t < BPT; ++t) {
     double2 a[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) a[q] = v[t + q * BPT];
+    double2 p[NPOW > 0 ? NPOW : 1];
     if constexpr (SC::ns(I) > 1) {
-      double2 u = tb.w[t % bases<SC, I>()];
+#pragma unroll
+      for (int j = 0; j < (TABLE ? NPOW : 1); ++j) {
+        double2 u = tb.w[t % Base<SC, I, TABLE>::kBases][j];
 #if defined(__HIP_DEVICE_COMPILE__)
-      // a copy the optimizer cannot see through: the powers of the base are
-      // formed in each transform, not kept live from one to the next
-      asm volatile("" : "+v"(u.x), "+v"(u.y));
+        // a copy the optimizer cannot see through: the products of the base are
+        // formed in each transform, not kept live from one to the next
+        asm volatile("" : "+v"(u.x), "+v"(u.y));
 #endif
-      if constexpr (SIGN > 0) u.y = -u.y;
-      dft<R, SIGN, true>(a, u);
+        if constexpr (SIGN > 0) u.y = -u.y;
+        p[j] = u;
+      }
+      if constexpr (!TABLE) powers<R>(p[0], p);
+      dft<R, SIGN, true>(a, p);
     } else {
-      dft<R, SIGN, false>(a, c2(1.0, 0.0));
+      dft<R, SIGN, false>(a, p);
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) v[t + q * BPT] = a[q];

@@ -132,6 +132,7 @@ struct Line {
   static constexpr int kRow = SC::kRow;
   static constexpr int kHalf = (L / 2) | 1;  // row of the r2c half exchange
   static constexpr bool kFull = NT == T * S;
+  static constexpr bool kTable = sizeof(ST) == 8;  // twiddle powers from the table
   static_assert(SC::valid() && SC::separable() && (N >= 2 || kZ), "schedule");
 
   // thread positions: (gA, sA) in mapping A, (gB, sB) in mapping B
@@ -154,9 +155,9 @@ struct Line {
   static constexpr bool in_b() {
     return !kZ && (kFwd ? I == N - 1 : I == 0);
   }
-  bfft::Base<SC, 1> w1;
-  bfft::Base<SC, (N > 2 ? 2 : 1)> w2;
-  bfft::Base<SC, (N > 3 ? 3 : 1)> w3;
+  bfft::Base<SC, 1, kTable> w1;
+  bfft::Base<SC, (N > 2 ? 2 : 1), kTable> w2;
+  bfft::Base<SC, (N > 3 ? 3 : 1), kTable> w3;
   __device__ __forceinline__ void load_twiddles(const double2* tw) {
     w1.load(tw, in_b<1>() ? sB : sA);
     if constexpr (N > 2) w2.load(tw, in_b<2>() ? sB : sA);
@@ -166,14 +167,14 @@ struct Line {
   __device__ __forceinline__ void stage(double2 (&v)[P]) const {
     constexpr int SIGN = kFwd ? -1 : 1;
     if constexpr (I == 0) {
-      bfft::Base<SC, 0> none{};
-      bfft::stage<SC, 0, SIGN>(v, none);
+      bfft::Base<SC, 0, kTable> none{};
+      bfft::stage<SC, 0, SIGN, kTable>(v, none);
     } else if constexpr (I == 1) {
-      bfft::stage<SC, 1, SIGN>(v, w1);
+      bfft::stage<SC, 1, SIGN, kTable>(v, w1);
     } else if constexpr (I == 2) {
-      bfft::stage<SC, 2, SIGN>(v, w2);
+      bfft::stage<SC, 2, SIGN, kTable>(v, w2);
     } else {
-      bfft::stage<SC, 3, SIGN>(v, w3);
+      bfft::stage<SC, 3, SIGN, kTable>(v, w3);
     }
   }
   // exchange I; FROM_B / TO_B: the mappings it is written and read in

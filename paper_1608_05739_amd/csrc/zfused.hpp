@@ -73,6 +73,8 @@ struct Budget {
   static constexpr int HELD_LDS = two ? held_lds(kTwo, 8) : (one >= 0 ? one : 0);
   static constexpr bool kPrefetch = !two || regs(NIN - HELD_LDS + 1) <= kTwo;
   static constexpr int waves = two ? 2 : 1;
+  // FP64: the twiddle powers of every stage from the table, where they fit
+  static constexpr bool kTable = ELEM == 8 && regs(NIN - HELD_LDS) + 36 <= (two ? kTwo : 480);
 };
 
 bool supported(int precision, int ndim, int src, int nz);

@@ -90,16 +90,17 @@ struct ZLine {
   using V = typename Store<ST>::V;
   static constexpr int P = SC::P, S = SC::S, N = SC::N, T = TL::T, NT = TL::NT;
   static constexpr bool kFull = NT == T * S;
+  static constexpr bool kTable = BU::kTable;
   static constexpr bool kWave = SC::kWave && kFull;
   static constexpr int kSlots = BU::HELD_LDS * P * NT;  // thread slots of held inputs (V)
   static_assert(SC::valid() && SC::separable() && N >= 2, "schedule");
 
   int g, s;
   bool live;
-  bfft::Base<SC, 1> w1;
-  bfft::Base<SC, (N > 2 ? 2 : 1)> w2;
-  bfft::Base<SC, (N > 3 ? 3 : 1)> w3;
-  bfft::Base<SC, (N > 4 ? 4 : 1)> w4;
+  bfft::Base<SC, 1, kTable> w1;
+  bfft::Base<SC, (N > 2 ? 2 : 1), kTable> w2;
+  bfft::Base<SC, (N > 3 ? 3 : 1), kTable> w3;
+  bfft::Base<SC, (N > 4 ? 4 : 1), kTable> w4;
 
   __device__ __forceinline__ ZLine() {
     const int tid = threadIdx.x;
@@ -117,16 +118,16 @@ struct ZLine {
   template <int I, int SIGN>
   __device__ __forceinline__ void stage(double2 (&v)[P]) const {
     if constexpr (I == 0) {
-      bfft::Base<SC, 0> none{};
-      bfft::stage<SC, 0, SIGN>(v, none);
+      bfft::Base<SC, 0, kTable> none{};
+      bfft::stage<SC, 0, SIGN, kTable>(v, none);
     } else if constexpr (I == 1) {
-      bfft::stage<SC, 1, SIGN>(v, w1);
+      bfft::stage<SC, 1, SIGN, kTable>(v, w1);
     } else if constexpr (I == 2) {
-      bfft::stage<SC, 2, SIGN>(v, w2);
+      bfft::stage<SC, 2, SIGN, kTable>(v, w2);
     } else if constexpr (I == 3) {
-      bfft::stage<SC, 3, SIGN>(v, w3);
+      bfft::stage<SC, 3, SIGN, kTable>(v, w3);
     } else {
-      bfft::stage<SC, 4, SIGN>(v, w4);
+      bfft::stage<SC, 4, SIGN, kTable>(v, w4);
     }
   }
   template <int SIGN, int I = 0>
