@@ -20,18 +20,21 @@ namespace lines {
 
 // A tile is T rows (lines) of one component, transformed by T S threads.  The
 // x and y passes transpose: on the strided side of a tile T consecutive
-// elements are one run of 8 T (FP32) or 16 T bytes (FP64), so T is 16 or 8
-// (128 bytes) as long as two tiles fit a CU's LDS, half of that for longer
-// lines, and as few as fit for the longest.
+// elements are one run of 8 T (FP32) or 16 T bytes (FP64).  T is 16 or 8 (128
+// bytes) as long as two tiles fit a CU's LDS, and is halved until they do:
+// neighbouring tiles run on one XCD and complete the lines in its L2, and a
+// second tile on the CU is worth more than longer runs (1152 points, FP32: 3.4
+// and 3.0 TB/s with 64-byte runs and one tile per CU, 4.3 and 3.5 with two).
+// FP64 keeps 64 bytes where one tile fits (2048 points forward: 4.3 TB/s,
+// 2.8 with two tiles of 32-byte runs).
 template <int L, int ELEM, bool TRANSPOSING>
 struct Tile {
-  using SC = bfft::Sched<L, false>;
+  using SC = bfft::Sched<L, ELEM == 8 ? bfft::kLine64 : bfft::kLine32>;
   static constexpr int rows() {
-    const int want = ELEM == 4 ? 16 : 8;
-    int t = want;
-    while (t > 1 && (t * SC::S > 512 || t * SC::kRow * 16 > 80 * 1024)) t /= 2;
-    if (TRANSPOSING)  // at least 64-byte runs where one tile fits the LDS
-      while (t < want / 2 && 2 * t * SC::S <= 1024 && 2 * t * SC::kRow * 16 <= 160 * 1024) t *= 2;
+    int t = ELEM == 4 ? 16 : 8;
+    while (t > 1 && (t * SC::S > 640 || t * SC::kRow * 16 > 80 * 1024)) t /= 2;
+    if (TRANSPOSING && ELEM == 8)
+      while (t < 4 && 2 * t * SC::S <= 1024 && 2 * t * SC::kRow * 16 <= 160 * 1024) t *= 2;
     while (t * SC::S < 128 && 2 * t * SC::kRow * 16 <= 40 * 1024) t *= 2;  // short lines: two waves
     return t;
   }

@@ -121,7 +121,7 @@ __device__ __forceinline__ double2 post_step(double2 w) {
 
 template <typename ST, int KIND, int L>
 struct Line {
-  using SC = bfft::Sched<L, false>;
+  using SC = bfft::Sched<L, sizeof(ST) == 8 ? bfft::kLine64 : bfft::kLine32>;
   using V = typename Store<ST>::V;
   static constexpr bool kX = KIND == kXFwd || KIND == kXInv;
   static constexpr bool kY = KIND == kYFwd || KIND == kYInv;
@@ -134,6 +134,11 @@ struct Line {
   static constexpr bool kFull = NT == T * S;
   static constexpr bool kTable = sizeof(ST) == 8;  // twiddle powers from the table
   static_assert(SC::valid() && SC::separable() && (N >= 2 || kZ), "schedule");
+
+  // waves per SIMD that the registers are limited to: at 18 and 24 points per
+  // thread the inverse x pass would take 258 registers and run alone on its
+  // SIMD (288 points FP32: 2.75 TB/s; 4.4 forward at 232 registers)
+  static constexpr int kWaves = P >= 18 ? 2 : (NT + 255) / 256;
 
   // thread positions: (gA, sA) in mapping A, (gB, sB) in mapping B
   int gA, sA, gB, sB;
@@ -198,6 +203,7 @@ struct Line {
 
 template <typename ST, int KIND, int L>
 __global__ void __launch_bounds__((Line<ST, KIND, L>::NT))
+    __attribute__((amdgpu_waves_per_eu(Line<ST, KIND, L>::kWaves)))
 fft_line_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict__ items,
                 int nitems, FieldPtrs fields, ST* __restrict__ ws) {
   using LN = Line<ST, KIND, L>;

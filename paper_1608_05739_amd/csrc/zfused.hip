@@ -13,7 +13,7 @@ struct Shape {
 Shape shape(int nz) {
   switch (nz) {
 #define PSATD_Z_SHAPE(LEN) \
-  case LEN: return Shape{Tile<LEN>::T, Tile<LEN>::NT, Tile<LEN>::T * bfft::Sched<LEN, true>::kRow * 16};
+  case LEN: return Shape{Tile<LEN>::T, Tile<LEN>::NT, Tile<LEN>::T * bfft::Sched<LEN, bfft::kFusedZ>::kRow * 16};
     PSATD_Z_A(PSATD_Z_SHAPE)
     PSATD_Z_B(PSATD_Z_SHAPE)
     PSATD_Z_C(PSATD_Z_SHAPE)
@@ -35,7 +35,7 @@ int slots(int src) {
     case kPstdVacuum: n = Budget<DIM, kPstdVacuum, L, ELEM>::HELD_LDS; break;
     default: n = Budget<DIM, kPstdJ, L, ELEM>::HELD_LDS; break;
   }
-  return n * bfft::Sched<L, true>::P * Tile<L>::NT * 2 * ELEM;
+  return n * bfft::Sched<L, bfft::kFusedZ>::P * Tile<L>::NT * 2 * ELEM;
 }
 template <int L>
 int slots_of(int precision, int ndim, int src) {

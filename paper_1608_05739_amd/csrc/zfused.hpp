@@ -30,7 +30,7 @@ constexpr int inputs(int dim, int src) {
 // sets of a 2D item are work of their own).
 template <int L>
 struct Tile {
-  using SC = bfft::Sched<L, true>;
+  using SC = bfft::Sched<L, bfft::kFusedZ>;
   static constexpr int round64(int n) { return (n + 63) / 64 * 64; }
   static constexpr int lines() {
     int best = 1;
@@ -53,7 +53,7 @@ struct Tile {
 // ran 51.8 us with it (spills) and 32.8 without (2048 x 512).
 template <int DIM, int SRC, int L, int ELEM>
 struct Budget {
-  using SC = bfft::Sched<L, true>;
+  using SC = bfft::Sched<L, bfft::kFusedZ>;
   static constexpr int NIN = inputs(DIM, SRC);
   static constexpr int kTwo = ELEM == 4 ? 264 : 230;  // estimates up to which two waves pay
   // held inputs, the transform, the rest

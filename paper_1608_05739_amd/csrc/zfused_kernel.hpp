@@ -84,7 +84,7 @@ struct Held<N, double> {
 
 template <typename ST, int DIM, int SRC, int L>
 struct ZLine {
-  using SC = bfft::Sched<L, true>;
+  using SC = bfft::Sched<L, bfft::kFusedZ>;
   using TL = Tile<L>;
   using BU = Budget<DIM, SRC, L, sizeof(ST)>;
   using V = typename Store<ST>::V;
