@@ -76,11 +76,14 @@ enum { PSATD_PATH_FUSED = 0, PSATD_PATH_PLAIN = 1 };
  * below or not); keep the fastest.  Grid and tile choices do not change
  * results; the radix schedule changes them in the last bits. */
 #define PSATD_FLAG_AUTOTUNE 0x1u
-/* Capture one step into a hipGraph at plan time (or in psatd_set_workspace when
- * the plan has no workspace yet); psatd_push then writes the field pointers
- * into a plan-owned device table (one small kernel) and replays the graph
- * nsteps times.  Pushes on a stream that the caller is capturing enqueue the
- * kernels themselves instead, so that the caller's graph records them. */
+/* Run a step the way that costs the fewest host calls and idle gaps.  Where a
+ * pass has several launches (one per line length), one step is captured into a
+ * hipGraph at plan time (or in psatd_set_workspace when the plan has no
+ * workspace yet) in which they run side by side; psatd_push then writes the
+ * field pointers into a plan-owned device table (one small kernel) and replays
+ * the graph nsteps times.  Where every pass is one launch, and for pushes on a
+ * stream that the caller is capturing, the kernels themselves are enqueued (in
+ * the second case the caller's graph records them). */
 #define PSATD_FLAG_GRAPH 0x2u
 #define PSATD_FLAG_NO_WORKSPACE 0x4u /* allocate no workspace: call psatd_set_workspace first */
 #define PSATD_FLAG_GENERIC_KERNELS 0x8u /* never pick shape-specialized kernels (cross-checks) */
@@ -189,7 +192,8 @@ psatd_status psatd_workspace_size(psatd_plan_t plan, size_t* bytes);
 /* Hand the plan a caller-owned device workspace of at least
  * psatd_workspace_size() bytes, 256-byte aligned.  Frees any plan-owned
  * workspace.  The caller keeps it alive until psatd_destroy.  With
- * PSATD_FLAG_GRAPH this (re)captures the step graph, which allocates. */
+ * PSATD_FLAG_GRAPH this (re)captures the step graph, if the step has one,
+ * which allocates. */
 psatd_status psatd_set_workspace(psatd_plan_t plan, void* device_ptr, size_t bytes);
 
 /* Advance the fields by nsteps steps, asynchronously on `hip_stream` (a
@@ -226,7 +230,7 @@ psatd_status psatd_push_scratch(psatd_plan_t plan, const psatd_fields* fields, i
 /* Like psatd_push, but records a HIP event pair around every pass on
  * `hip_stream`, synchronizes at the end and writes the mean duration of each
  * pass in milliseconds to ms_per_pass[0 .. npass-1] (npass from
- * psatd_pass_count).  A PSATD_FLAG_GRAPH plan launches each pass as a graph
+ * psatd_pass_count).  A plan that replays a graph launches each pass as a graph
  * of its own, captured at plan time like the step's graph (a pass launched
  * once per line length runs those launches as parallel branches), so each
  * pass is timed as the step's graph runs it; other plans enqueue the
