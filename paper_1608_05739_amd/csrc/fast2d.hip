@@ -14,6 +14,7 @@
 // wave-private LDS exchanges in FP64 (real and imaginary halves in turn).
 #include <hip/hip_runtime.h>
 
+#include "bfft.hpp"
 #include "fast2d.hpp"
 #include "fft.hpp"
 #include "groups.hpp"
@@ -457,9 +458,21 @@ constexpr int kZtStep = 584;  // W4096^(64 k2), k2 < 8: its step over q
 constexpr int kZtCount = 592;
 
 
-template <int SIGN>
+// v[k] <- sum_q v[q] w^q exp(-2 pi i q k / 8): the twiddles are part of the
+// butterflies (84 operations; 108 as seven products, the powers and a DFT of
+// 8).  The pass is bound by its FP64 operations at two waves per SIMD: 397 ->
+// 381 us with sources, 305 -> 298 in vacuum at 4096 x 4096.  (The x passes at
+// 2048 points are not: the same change there spilled and took x_fwd from 434
+// to 454 us.)
+__device__ __forceinline__ void dft8_twiddled(double2 (&v)[8], double2 w) {
+  double2 p[bfft::power_count(8)];
+  bfft::powers<8>(w, p);
+  bfft::dft<8, -1, true>(v, p);
+}
+
+// v[q] <- v[q] conj(w)^q
 __device__ __forceinline__ void twiddle8(double2 (&v)[8], double2 w) {
-  if constexpr (SIGN > 0) w.y = -w.y;
+  w.y = -w.y;
   double2 wq = w;
   v[1] = cmul(v[1], w);
 #pragma unroll
@@ -500,7 +513,7 @@ __device__ __forceinline__ ZIdx make_zidx() {
 // across the whole kernel.
 __device__ __forceinline__ void fwd512(double2 (&v)[8], double2* buf, const ZIdx& x,
                                        const double2* zt) {
-  DFT<8, -1>::run(v);  // stage 1 (Ns = 1), mapping A; outputs 8 j + q
+  bfft::dft<8, -1, false>(v, nullptr);  // stage 1 (Ns = 1), mapping A; outputs 8 j + q
   double2* wa = buf + x.baseA;
 #pragma unroll
   for (int q = 0; q < 8; ++q) wa[q] = v[q];
@@ -510,16 +523,14 @@ __device__ __forceinline__ void fwd512(double2 (&v)[8], double2* buf, const ZIdx
 #pragma unroll
   for (int q = 0; q < 8; ++q) v[q] = b1[64 * q];
   // stage 2: Ns = 8, k = j mod 8, w = exp(-2 pi i k / 64); outputs 8 (j - k) + k + 8 q
-  twiddle8<-1>(v, lds_twiddle(zt, kZtS2 + (x.jB & 7)));
-  DFT<8, -1>::run(v);
+  dft8_twiddled(v, lds_twiddle(zt, kZtS2 + (x.jB & 7)));
 #pragma unroll
   for (int q = 0; q < 8; ++q) b2[8 * q] = v[q];
   wave_lds_sync();
 #pragma unroll
   for (int q = 0; q < 8; ++q) v[q] = b1[64 * q];
   // stage 3: Ns = 64, k = j, w = exp(-2 pi i j / 512); outputs j + 64 q
-  twiddle8<-1>(v, lds_twiddle(zt, kZtS3 + x.jB));
-  DFT<8, -1>::run(v);
+  dft8_twiddled(v, lds_twiddle(zt, kZtS3 + x.jB));
 }
 
 // Inverse (unnormalized, the adjoint of fwd512): v holds elements jB + 64 q of
@@ -530,16 +541,16 @@ __device__ __forceinline__ void inv512(double2 (&v)[8], double2* buf, const ZIdx
   double2* b1 = buf + x.baseB1;
   double2* b2 = buf + x.baseB2;
   // adjoint of stage 3
-  DFT<8, 1>::run(v);
-  twiddle8<1>(v, lds_twiddle(zt, kZtS3 + x.jB));  // conjugate twiddles after the butterflies
+  bfft::dft<8, 1, false>(v, nullptr);
+  twiddle8(v, lds_twiddle(zt, kZtS3 + x.jB));  // conjugate twiddles after the butterflies
 #pragma unroll
   for (int q = 0; q < 8; ++q) b1[64 * q] = v[q];
   wave_lds_sync();
 #pragma unroll
   for (int q = 0; q < 8; ++q) v[q] = b2[8 * q];
   // adjoint of stage 2
-  DFT<8, 1>::run(v);
-  twiddle8<1>(v, lds_twiddle(zt, kZtS2 + (x.jB & 7)));
+  bfft::dft<8, 1, false>(v, nullptr);
+  twiddle8(v, lds_twiddle(zt, kZtS2 + (x.jB & 7)));
 #pragma unroll
   for (int q = 0; q < 8; ++q) b1[64 * q] = v[q];
   __syncthreads();
@@ -547,7 +558,7 @@ __device__ __forceinline__ void inv512(double2 (&v)[8], double2* buf, const ZIdx
 #pragma unroll
   for (int q = 0; q < 8; ++q) v[q] = ra[q];
   // adjoint of stage 1, mapping A
-  DFT<8, 1>::run(v);
+  bfft::dft<8, 1, false>(v, nullptr);
 }
 
 // Loads of one component column into FP32 registers (mapping A, positions
