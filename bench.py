@@ -84,11 +84,11 @@ def pass_of_kernel(name):
     for key, pname in (("x_fwd_kernel", "x_r2c_fwd"), ("z_fused_kernel", "z_fused"),
                        ("x_inv_kernel", "x_c2r_inv"), ("fused_z_kernel", "z_fused"),
                        ("wave_z_fused", "z_fused"), ("wave_z3_fused", "z_fused"),
-                       ("wave_z_set", "z_fused"),
+                       ("wave_z_set", "z_fused"), ("fft_z_kernel", "z_fused"),
                        ("update_kernel", "update")):
         if key in name:
             return pname
-    m = (re.search(r"(?:line_pass_kernel|ct_line_kernel)<[^,<>]+, ?(\d)", name)
+    m = (re.search(r"(?:line_pass_kernel|ct_line_kernel|fft_line_kernel)<[^,<>]+, ?(\d)", name)
          or re.search(r"wave_x_kernel<(\d)", name))
     if m:
         return LINE_KINDS[m.group(1)]
