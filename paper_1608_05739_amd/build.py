@@ -18,7 +18,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libpsatd.so")
-SOURCES = ["zfused_c.hip", "zfused_d.hip", "zfused_b.hip", "zfused_e.hip", "zfused_a.hip",
+SOURCES = ["zfused_rho_f64.hip", "zfused_j_f64.hip", "zfused_rho_f32.hip", "zfused_j_f32.hip",
+           "zfused_vacuum_f64.hip", "zfused_vacuum_f32.hip", "zfused_c.hip", "zfused_d.hip", "zfused_b.hip", "zfused_e.hip", "zfused_a.hip",
            "zfused_f.hip", "lines_large.hip", "lines_long.hip", "lines_mid.hip", "lines_small.hip",
            "kernels.hip", "fast2d.hip", "lines.hip", "zfused.hip", "domain.hip", "fdtd.hip", "api.cpp"]
 

@@ -147,7 +147,8 @@ enum PassType { kLine = 0, kFused = 1, kUpdate = 2, kFastXFwd = 3, kFastZ = 4, k
 
 // One launch of a pass compiled per length: the work items of one line length.
 struct SubLaunch {
-  int L = 0;
+  int L = 0;       // the line length; family launches: the longest
+  int family = 0;  // zfused::Family of a z launch over several lengths, else 0
   int first = 0;  // index of its first work item within the pass's list
   int nitems = 0;
   LaunchShape shape{};
@@ -717,7 +718,10 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
         return fail(PSATD_ERR_STATE, "z_fused (fixed length): item out of range");
       bool in_sub = false;
       for (const SubLaunch& sub : ps.subs)
-        in_sub = in_sub || (i >= sub.first && i < sub.first + sub.nitems && sub.L == P.nz);
+        in_sub = in_sub || (i >= sub.first && i < sub.first + sub.nitems &&
+                            (sub.family ? zfused::family(plan->cfg.precision, P.ndim, plan->src_form,
+                                                         P.nz) == sub.family
+                                        : sub.L == P.nz));
       if (!in_sub) return fail(PSATD_ERR_STATE, "z_fused (fixed length): item outside its length's launch");
       continue;
     }
@@ -838,39 +842,53 @@ bool fixed_z_eligible(const psatd_plan_s* plan) {
   return true;
 }
 
-// Work items of up to zfused::lines_per_item() z lines, one launch per length.
+// Work items of up to zfused::lines_per_item() z lines, one launch per length,
+// or per family of lengths of which the plan has several (longest lines first).
 Pass make_fixed_z_pass(const psatd_plan_s* plan, std::vector<WorkItem>& items) {
   Pass ps;
   ps.type = kWaveZ;
   ps.name = "z_fused";
   const size_t first = items.size();
+  const int prec = plan->cfg.precision;
   double bytes = 0.0;
-  std::set<int> lengths;
+  std::set<int, std::greater<int>> lengths;
   for (const PatchDev& P : plan->host_patches) lengths.insert(P.nz);
+  std::vector<std::pair<int, std::vector<int>>> groups;  // family, lengths
+  for (int L : lengths) {
+    const int fam = zfused::family(prec, plan->ndim, plan->src_form, L);
+    auto same = std::find_if(groups.begin(), groups.end(),
+                             [&](const auto& g) { return fam != 0 && g.first == fam; });
+    if (same != groups.end()) same->second.push_back(L);
+    else groups.push_back({fam, {L}});
+  }
   size_t lds = 0;
   int block = 64, total = 0;
-  for (int L : lengths) {
+  for (const auto& g : groups) {
     SubLaunch sub;
-    sub.L = L;
+    sub.L = g.second[0];
+    sub.family = g.second.size() > 1 ? g.first : 0;
     sub.first = static_cast<int>(items.size() - first);
-    const int T = zfused::lines_per_item(L);
-    for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
-      const PatchDev& P = plan->host_patches[pi];
-      if (P.nz != L) continue;
-      const int nlines = P.mx * P.ny;
-      for (int l = 0; l < nlines; l += T)
-        items.push_back(WorkItem{static_cast<int>(pi), l, std::min(T, nlines - l), -1});
-      const double cells = static_cast<double>(P.nx) * P.ny * P.nz;
-      bytes += (plan->nin + 6) * cells * plan->elem;
+    for (int L : g.second) {
+      const int T = zfused::lines_per_item(L);
+      ps.lines = std::max(ps.lines, T);
+      for (size_t pi = 0; pi < plan->host_patches.size(); ++pi) {
+        const PatchDev& P = plan->host_patches[pi];
+        if (P.nz != L) continue;
+        const int nlines = P.mx * P.ny;
+        for (int l = 0; l < nlines; l += T)
+          items.push_back(WorkItem{static_cast<int>(pi), l, std::min(T, nlines - l), -1});
+        const double cells = static_cast<double>(P.nx) * P.ny * P.nz;
+        bytes += (plan->nin + 6) * cells * plan->elem;
+      }
     }
     sub.nitems = static_cast<int>(items.size() - first) - sub.first;
     sub.full = zfused::workgroups(plan->ndim, sub.nitems);
-    const size_t sub_lds = zfused::lds_bytes(plan->cfg.precision, plan->ndim, plan->src_form, L);
-    sub.shape = LaunchShape{sub.full, zfused::block(L), sub_lds};
+    const size_t sub_lds = sub.family ? zfused::family_lds_bytes(prec, plan->src_form, sub.family)
+                                      : zfused::lds_bytes(prec, plan->ndim, plan->src_form, sub.L);
+    sub.shape = LaunchShape{sub.full, sub.family ? zfused::kFamilyBlock : zfused::block(sub.L), sub_lds};
     lds = std::max(lds, sub_lds);
     block = std::max(block, sub.shape.block);
     total += sub.full;
-    ps.lines = std::max(ps.lines, T);
     ps.subs.push_back(sub);
   }
   ps.nitems = static_cast<int>(items.size() - first);
@@ -946,6 +964,9 @@ psatd_status enqueue_pass(const psatd_plan_s* plan, const Pass& ps, const FieldP
       break;
     case kWaveZ:
       e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
+        if (sub.family)
+          return zfused::launch_family(plan->cfg.precision, plan->src_form, sub.family, sub.shape.grid,
+                                       t, plan->d_patches, ps.d_items + sub.first, sub.nitems, ws, ph);
         return zfused::launch(plan->cfg.precision, plan->ndim, plan->src_form, sub.L, sub.shape.grid,
                               t, plan->d_patches, ps.d_items + sub.first, sub.nitems, ws, ph);
       });

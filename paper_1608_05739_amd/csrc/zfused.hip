@@ -64,6 +64,42 @@ int lds_bytes(int precision, int ndim, int src, int nz) {
   }
 }
 
+int family(int precision, int ndim, int src, int nz) {
+  if (ndim != 2 || src_is_pstd(src) || !supported(precision, ndim, src, nz)) return kNoFamily;
+  switch (nz) {
+#define PSATD_Z_FAMILY_LABEL(LEN) case LEN:
+    PSATD_Z_POW2(PSATD_Z_FAMILY_LABEL)
+    return kPow2;
+    PSATD_Z_3POW2(PSATD_Z_FAMILY_LABEL)
+    return k3Pow2;
+    default: return kNoFamily;
+  }
+}
+int family_lds_bytes(int precision, int src, int fam) {
+  switch (src) {
+    case kVacuum: return precision == 0 ? family_lds_vacuum_f32(fam) : family_lds_vacuum_f64(fam);
+    case kRho: return precision == 0 ? family_lds_rho_f32(fam) : family_lds_rho_f64(fam);
+    default: return precision == 0 ? family_lds_j_f32(fam) : family_lds_j_f64(fam);
+  }
+}
+hipError_t launch_family(int precision, int src, int fam, int grid, hipStream_t stream,
+                         const PatchDev* patches, const WorkItem* items, int nitems, void* ws,
+                         Physics ph) {
+  switch (src) {
+    case kVacuum:
+      return precision == 0
+                 ? launch_family_vacuum_f32(fam, grid, stream, patches, items, nitems, ws, ph)
+                 : launch_family_vacuum_f64(fam, grid, stream, patches, items, nitems, ws, ph);
+    case kRho:
+      return precision == 0 ? launch_family_rho_f32(fam, grid, stream, patches, items, nitems, ws, ph)
+                            : launch_family_rho_f64(fam, grid, stream, patches, items, nitems, ws, ph);
+    case kJForm:
+      return precision == 0 ? launch_family_j_f32(fam, grid, stream, patches, items, nitems, ws, ph)
+                            : launch_family_j_f64(fam, grid, stream, patches, items, nitems, ws, ph);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch(int precision, int ndim, int src, int nz, int grid, hipStream_t stream,
                   const PatchDev* patches, const WorkItem* items, int nitems, void* ws, Physics ph) {
   switch (nz) {

@@ -88,6 +88,36 @@ inline int workgroups(int ndim, int nitems) { return ndim == 2 ? 2 * nitems : ni
 hipError_t launch(int precision, int ndim, int src, int nz, int grid, hipStream_t stream,
                   const PatchDev* patches, const WorkItem* items, int nitems, void* ws, Physics ph);
 
+// Families of lengths that a 2D plan runs in one launch when it has several of
+// a family (fft_zs_kernel): the points per thread, the threads per workgroup
+// and so the registers are the same within a family, and a launch per length
+// costs about 6 us to fork and join in the step graph.  (One launch for both
+// families, and for families of different points per thread in the line
+// passes, gave the short lengths the registers of the long ones: 64 x 64
+// patches, x pass 69 -> 138 us.)
+#define PSATD_Z_POW2(X) X(32) X(64) X(128) X(256) X(512)
+#define PSATD_Z_3POW2(X) X(48) X(96) X(192) X(384)
+enum Family { kNoFamily = 0, kPow2 = 1, k3Pow2 = 2 };
+constexpr int kFamilyBlock = 256;
+// The family whose kernel is compiled for this form and takes the length.
+int family(int precision, int ndim, int src, int nz);
+int family_lds_bytes(int precision, int src, int fam);
+// One launch covers the items of the patches with lengths of the family.
+hipError_t launch_family(int precision, int src, int fam, int grid, hipStream_t stream,
+                         const PatchDev* patches, const WorkItem* items, int nitems, void* ws,
+                         Physics ph);
+// (one translation unit per form and precision)
+#define PSATD_ZS_FORM(name)                                                                        \
+  hipError_t launch_family_##name(int fam, int grid, hipStream_t stream, const PatchDev* patches,  \
+                                  const WorkItem* items, int nitems, void* ws, Physics ph);        \
+  int family_lds_##name(int fam)
+PSATD_ZS_FORM(vacuum_f32);
+PSATD_ZS_FORM(rho_f32);
+PSATD_ZS_FORM(j_f32);
+PSATD_ZS_FORM(vacuum_f64);
+PSATD_ZS_FORM(rho_f64);
+PSATD_ZS_FORM(j_f64);
+
 #define PSATD_Z_GROUP(name)                                                                        \
   hipError_t launch_##name(int precision, int ndim, int src, int nz, int grid, hipStream_t stream, \
                            const PatchDev* patches, const WorkItem* items, int nitems, void* ws,   \

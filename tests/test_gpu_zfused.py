@@ -77,3 +77,43 @@ def test_pstd_sets(L, mode):
     err = np.sqrt(sum(np.sum((g - r) ** 2) for g, r in zip(got, ref)) / sum(np.sum(r * r) for r in ref))
     say(f"pstd sets {L} {mode}: {err:.1e}")
     assert err < TOL["fp32"]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("mode", ["vacuum", "rho", "j"])
+@pytest.mark.parametrize("graph", [False, True])
+def test_families_of_lengths_equal_patches_alone(precision, mode, graph):
+    """A batch with several 2^k and 3 2^k z lengths runs each family in one launch;
+    a patch alone runs the kernel of its length.  27, 6 and 36 columns leave a short
+    last item at every length.  Both round the same FP64 arithmetic to storage at the
+    same places, so they differ by its last bits at most: the bounds are a few
+    rounding units of the storage."""
+    import torch
+    lengths = [32, 512, 48, 72, 64, 384, 54, 128, 192, 256, 96, 144]
+    patches = [pk.Patch(2, ((54, 12, 72)[i % 3], 1, L), (1 / 32,) * 3, 1 / 40) for i, L in enumerate(lengths)]
+    dtype = torch.float32 if precision == "fp32" else torch.float64
+    gen = torch.Generator().manual_seed(7)
+    ncomp = {"vacuum": 6, "j": 9, "rho": 11}[mode]
+    batch = pk.Plan(patches, precision=precision, source_mode=mode, graph=graph)
+    data = torch.randn(ncomp, batch.total_elements, generator=gen, dtype=torch.float64).to(dtype)
+
+    def push(plan, comps):
+        t = [c.clone().cuda() for c in comps]
+        args = [t[0:3], t[3:6]] + ([t[6:9]] if ncomp > 6 else []) + (t[9:11] if ncomp > 9 else [])
+        plan.push(*args)
+        torch.cuda.synchronize()
+        return [x.cpu().double() for x in t[:6]]
+
+    say(f"z families {precision} {mode} graph={graph}")
+    got = push(batch, data)
+    offsets = batch.offsets
+    batch.close()
+    bound = 5e-7 if precision == "fp32" else 1e-14
+    for p, off in zip(patches, offsets):
+        alone = pk.Plan([p], precision=precision, source_mode=mode)
+        n = alone.total_elements
+        ref = push(alone, data[:, off:off + n])
+        alone.close()
+        for a, b in zip(got, ref):
+            d = torch.linalg.vector_norm(a[off:off + p.cells] - b[:p.cells])
+            assert d <= bound * torch.linalg.vector_norm(b[:p.cells]), (p, float(d))
