@@ -70,9 +70,10 @@ def measured_traffic(workload, kernel):
     return ent.get("bytes_per_launch")
 
 
-# rocprofv3 kernel names -> pass names: the 4096 x 4096 kernels, the wave
-# z pass, and the line kernels whose template argument KIND names the pass
-# (line_pass_kernel<S, KIND, PPT>, ct_line_kernel<S, KIND, L>,
+# rocprofv3 kernel names -> pass names: the 4096 x 4096 kernels, the fused
+# z passes, and the line kernels whose template argument KIND names the pass
+# (line_pass_kernel<S, KIND, PPT>, fft_line_kernel<S, KIND, L>, and in older
+# traces ct_line_kernel<S, KIND, L>,
 # wave_x_kernel<KIND, L>; KIND 0 x fwd, 1 x inv, 2 y fwd, 3 y inv, 4 z fwd,
 # 5 z inv)
 LINE_KINDS = {"0": "x_r2c_fwd", "1": "x_c2r_inv", "2": "y_c2c_fwd", "3": "y_c2c_inv",
@@ -85,6 +86,7 @@ def pass_of_kernel(name):
                        ("x_inv_kernel", "x_c2r_inv"), ("fused_z_kernel", "z_fused"),
                        ("wave_z_fused", "z_fused"), ("wave_z3_fused", "z_fused"),
                        ("wave_z_set", "z_fused"), ("fft_z_kernel", "z_fused"),
+                       ("fft_zs_kernel", "z_fused"),
                        ("update_kernel", "update")):
         if key in name:
             return pname

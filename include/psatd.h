@@ -98,12 +98,12 @@ enum { PSATD_PATH_FUSED = 0, PSATD_PATH_PLAIN = 1 };
  *   B^{n+1/2} = B^{n-1/2} - dt curl E^n,
  *   E^{n+1}   = E^n + dt (c^2 curl B^{n+1/2} - J^{n+1/2} / eps0)
  * with curl -> i k x.  source_mode must be PSATD_VACUUM or PSATD_SOURCES_J
- * (PSTD uses no rho); the generic kernels run it.  Planning fails with
+ * (PSTD uses no rho).  Planning fails with
  * PSATD_ERR_INVALID_ARG when c dt |k|max / 2 > 1 for a patch (its Courant
  * condition; |k|max over the patch's k table). */
 #define PSATD_FLAG_PSTD 0x20u
-/* The generic line passes (any size other than the 4096 x 4096 2D grid)
- * factor each line into radix-4 stages (then one radix-2 and the radix-3
+/* Run the generic line passes instead of those with compile-time lengths (not
+ * on the 4096 x 4096 2D grid), and factor each line into radix-4 stages (then one radix-2 and the radix-3
  * stages) at 4 points per thread, instead of the default radices of at most 8
  * at 8 points per thread.  Half the registers, twice the waves per SIMD:
  * faster on short lines (2D patches with sides of a few hundred cells),
@@ -291,8 +291,8 @@ typedef struct {
 } psatd_domain_desc;
 
 /* Build the decomposition and its internal plan (same config; the config's
- * flags apply to it; its x passes are the generic kernels, which read and
- * write through the patches' places in the global grid).  Allocates the
+ * flags apply to it; its x passes read and write through the patches' places
+ * in the global grid).  Allocates the
  * plan's workspace.  Errors as psatd_plan; PSATD_ERR_UNSUPPORTED_SIZE if a
  * local side is not a supported length; PSATD_ERR_INVALID_ARG for an odd x
  * guard on a split x axis. */
