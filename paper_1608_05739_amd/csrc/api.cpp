@@ -145,7 +145,8 @@ struct DeviceGuard {
 enum PassType { kLine = 0, kFused = 1, kUpdate = 2, kFastXFwd = 3, kFastZ = 4, kFastXInv = 5,
                 kWaveZ = 6, kWaveX = 7 };
 
-// One launch of a pass compiled per length: the work items of one line length.
+// One launch of a pass compiled per length: the work items of one line length,
+// or of a family of z lengths.
 struct SubLaunch {
   int L = 0;       // the line length; family launches: the longest
   int family = 0;  // zfused::Family of a z launch over several lengths, else 0
@@ -901,9 +902,10 @@ Pass make_fixed_z_pass(const psatd_plan_s* plan, std::vector<WorkItem>& items) {
 // A pass launched once per line length runs its launches as up to kMaxBranches
 // parallel branches of the captured graph, the first on the stream itself.
 // More branches cost more to fork and join than they overlap, and one leaves
-// the chip idle at the end of each launch: 64 patches of seven sides with
-// sources, FP32, take 398, 312, 300, 307, 309, 337 and 319 us per step with 1
-// to 7 branches.
+// the chip idle at the end of each launch.  us per step with 1, 2, 3, 4 and 7
+// branches: 64 patches of seven sides with sources FP32 318, 274, 273, 302, 287;
+// 256 patches vacuum 664, 598, 590, 607, 601; 128 patches with sources FP64 670,
+// 566, 543, 576, 552.
 constexpr size_t kMaxBranches = 3;
 size_t branches(const Pass& ps) { return std::min(ps.subs.size(), kMaxBranches); }
 
