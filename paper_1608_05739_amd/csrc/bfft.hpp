@@ -136,10 +136,8 @@ constexpr int power(int R, int j) {
   if (R % 2 == 0) return j == 0 ? 1 : 2 * power(R / 2, j - 1);
   return j < 2 ? j + 1 : 3 * (j - 1);
 }
-// The same from the base alone.  Each squaring doubles the relative error of
-// the table's rounding, which FP32 storage does not show (2^-24); FP64 storage
-// takes the powers from the table (a 1024-point transform is then off by
-// 2.6e-16 instead of 4.0e-16).
+// The same from the base alone, for FP32 storage: each squaring doubles the
+// relative error of the table's rounding, which 2^-24 does not show.
 template <int R>
 PSATD_HD void powers(double2 u, double2* p) {
   if constexpr (R == 1) {
@@ -240,6 +238,77 @@ PSATD_HD void dft(double2 (&a)[R], const double2* p) {
   }
 }
 
+// Where the twiddles of a stage come from.  FP32 storage keeps the base of each
+// butterfly and squares it (kSquares).  FP64 storage takes them from the plan's
+// table, so that its transforms are not less exact than those of the generic
+// kernels, whose stages of at most 8 points multiply powers up: read once and
+// held (kTable, the line passes), or read from a copy in LDS (kShared, most fused
+// z passes, whose registers hold a set of inputs).  Relative error of a transform
+// of Gaussian values, 1e-16, squared / from the table / generic: 192 points 3.4 /
+// 1.8 / 2.5, 432 points 3.9 / 2.0 / 2.3, 1024 points 3.3 / 2.3 / 3.3.
+enum Twiddles { kSquares, kTable, kShared };
+
+// Radices 6, 12, 18 and 24.  Their butterflies with folded twiddles multiply the
+// base by constants of both factors (144 points: 2.2 with folded twiddles from
+// the table, 2.0 the generic kernels); FP64 storage multiplies the points by
+// their twiddles and transforms them by the prime-factor algorithm, which has no
+// twiddles of its own (1.7).  Both forms of a radix-12 butterfly are about 160
+// operations.
+constexpr bool mixed(int R) { return R % 6 == 0; }
+
+// Of the powers that such a butterfly takes, those below W and the multiples of W
+// come from the table and the others are one product each: 8 instead of 23 values
+// for 24 points, 5 instead of 11 for 12 (error at 1152 points 2.05 instead of
+// 2.00; 2D rho form of 2592 x 768, FP64, fused z pass: 128 us, 131 with all 11
+// read from LDS).
+constexpr int split(int R) { return R == 18 ? 3 : 4; }  // W
+
+// Twiddles a butterfly of radix R takes, and the power of the base that each is.
+constexpr int twiddle_count(int R, Twiddles tw) {
+  if (tw == kSquares) return 1;
+  if (!mixed(R)) return power_count(R);
+  return split(R) - 1 + (R - 1) / split(R);
+}
+constexpr int twiddle_power(int R, Twiddles tw, int j) {
+  if (tw == kSquares || !mixed(R)) return power(R, j);
+  return j < split(R) ? j + 1 : split(R) * (j - split(R) + 2);
+}
+// Twiddle u^q of a mixed radix from those (p).
+template <int R, int Q>
+PSATD_HD double2 twiddle(const double2* p) {
+  constexpr int W = split(R), lo = Q % W, hi = Q / W;
+  if constexpr (hi == 0) return p[Q - 1];
+  else if constexpr (lo == 0) return p[W - 2 + hi];
+  else return mul(p[lo - 1], p[W - 2 + hi]);
+}
+
+// In-place DFT of length R = A B, A a power of two and B = 3 or 9, by the
+// prime-factor algorithm (Good 1958): input (B i + A j) mod R is element (i, j)
+// of a two-dimensional transform, whose element (k mod A, k mod B) is output k.
+// Other lengths as dft without twiddles.
+template <int R, int SIGN>
+PSATD_HD void dft_prime_factor(double2 (&a)[R]) {
+  if constexpr (!mixed(R)) {
+    dft<R, SIGN, false>(a, nullptr);
+  } else {
+    constexpr int B = R % 9 == 0 ? 9 : 3, A = R / B;
+    double2 y[B][A];
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+      double2 t[B];
+#pragma unroll
+      for (int j = 0; j < B; ++j) t[j] = a[(B * i + A * j) % R];
+      dft<B, SIGN, false>(t, nullptr);
+#pragma unroll
+      for (int j = 0; j < B; ++j) y[j][i] = t[j];
+    }
+#pragma unroll
+    for (int j = 0; j < B; ++j) dft<A, SIGN, false>(y[j], nullptr);
+#pragma unroll
+    for (int k = 0; k < R; ++k) a[k] = y[k % B][k % A];
+  }
+}
+
 // ------------------------------------------------------------------ schedules
 // P points per thread and up to five radices, in the order of the stages.
 struct Radices {
@@ -292,11 +361,15 @@ constexpr Radices line_radices(int L) {
 
 // FP64 storage: the same, except where 18 or 24 points of 16 bytes leave too few
 // waves (288 points, x passes of 16 MiB components: 4.3 forward and 3.7 TB/s
-// inverse as 24.12, 5.3 and 5.2 as 12.2.12).
+// inverse as 24.12, 5.3 and 5.2 as 12.2.12) or spill with the twiddles (1728
+// points, x passes of 4.0 M cells: 241 and 175 us as 24.3.24, 191 and 112 as
+// 12.12.12; 1152 points 152 and 88 as 24.2.24, 179 and 121 as 12.4.2.12).
 constexpr Radices line_radices_f64(int L) {
   switch (L) {
     case 216: return {12, 3, {6, 3, 12}};
     case 288: return {12, 3, {12, 2, 12}};
+    case 864: return {12, 3, {12, 6, 12}};
+    case 1728: return {12, 3, {12, 12, 12}};
     default: return line_radices(L);
   }
 }
@@ -423,51 +496,103 @@ constexpr int bases() {
   if (ns % SC::S == 0) return ns / SC::S < bpt ? ns / SC::S : bpt;
   return bpt;
 }
-// What a thread keeps of them: the base alone, or (TABLE) its powers too.
-template <typename SC, int I, bool TABLE>
+constexpr int at_least_one(int n) { return n > 0 ? n : 1; }
+
+// The thread's twiddles of stage I: get(t, j) is twiddle j of butterfly t.
+// Held in registers:
+template <typename SC, int I, Twiddles TW>
 struct Base {
-  static constexpr int kPow = TABLE ? power_count(SC::radix(I)) : 1;
-  static constexpr int kBases = bases<SC, I>() > 0 ? bases<SC, I>() : 1;
-  double2 w[kBases][kPow > 0 ? kPow : 1];
+  static constexpr int kCount = twiddle_count(SC::radix(I), TW);
+  static constexpr int kBases = at_least_one(bases<SC, I>());
+  double2 w[kBases][kCount];
   PSATD_HD void load(const double2* tw, int s) {
 #pragma unroll
     for (int t = 0; t < bases<SC, I>(); ++t) {
       const int i = twiddle_index<SC, I>(s, t);
-      static_for<0, kPow>([&](auto jc) __attribute__((always_inline)) {
-        constexpr int e = TABLE ? power(SC::radix(I), decltype(jc)::value) : 1;
-        w[t][decltype(jc)::value] = gload(tw, i * e);
+      static_for<0, kCount>([&](auto jc) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value, e = twiddle_power(SC::radix(I), TW, j);
+        w[t][j] = gload(tw, i * e);
       });
     }
   }
+  PSATD_HD double2 get(int t, int j) const { return w[t % kBases][j]; }
+};
+
+// The LDS copy of every stage's twiddles: twiddle j of the butterflies with
+// j mod Ns = k at [j][k], so that neighbouring threads read neighbouring
+// elements.  First element of stage I's (I = SC::N: the size).
+template <typename SC>
+constexpr int shared_offset(int I) {
+  int n = 0;
+  for (int i = 1; i < I; ++i) n += twiddle_count(SC::radix(i), kShared) * SC::ns(i);
+  return n;
+}
+// Thread `tid` of `nt` writes its part (the caller synchronizes).
+template <typename SC, int I = 1>
+PSATD_HD void fill_shared(double2* lds, const double2* tw, int tid, int nt) {
+  if constexpr (I < SC::N) {
+    constexpr int R = SC::radix(I), ns = SC::ns(I), step = SC::L / (ns * R);
+    static_for<0, twiddle_count(R, kShared)>([&](auto jc) __attribute__((always_inline)) {
+      constexpr int j = decltype(jc)::value, e = step * twiddle_power(R, kShared, j);
+      constexpr int first = shared_offset<SC>(I) + j * ns;
+      for (int k = tid; k < ns; k += nt) lds[first + k] = gload(tw, k * e);
+    });
+    fill_shared<SC, I + 1>(lds, tw, tid, nt);
+  }
+}
+template <typename SC, int I>
+struct Base<SC, I, kShared> {
+  static constexpr int kBases = at_least_one(bases<SC, I>());
+  const double2* p[kBases];
+  PSATD_HD void load(const double2* lds, int s) {
+#pragma unroll
+    for (int t = 0; t < bases<SC, I>(); ++t) {
+      constexpr int first = shared_offset<SC>(I);
+      p[t] = lds + first + (s + SC::S * t) % SC::ns(I);
+    }
+  }
+  PSATD_HD double2 get(int t, int j) const { return p[t % kBases][j * SC::ns(I)]; }
 };
 
 // Stage I on the thread's points: v[t + q P/R] is input q of butterfly t, and
 // output q after it.
-template <typename SC, int I, int SIGN, bool TABLE>
-PSATD_HD void stage(double2 (&v)[SC::P], const Base<SC, I, TABLE>& tb) {
+template <typename SC, int I, int SIGN, Twiddles TW>
+PSATD_HD void stage(double2 (&v)[SC::P], const Base<SC, I, TW>& tb) {
   constexpr int R = SC::radix(I), BPT = SC::P / R, NPOW = power_count(R);
+  constexpr int COUNT = twiddle_count(R, TW);
+  constexpr bool products = TW != kSquares && mixed(R);
 #pragma unroll
   for (int t = 0; t < BPT; ++t) {
     double2 a[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) a[q] = v[t + q * BPT];
-    double2 p[NPOW > 0 ? NPOW : 1];
     if constexpr (SC::ns(I) > 1) {
+      double2 p[COUNT > NPOW ? COUNT : NPOW];
 #pragma unroll
-      for (int j = 0; j < (TABLE ? NPOW : 1); ++j) {
-        double2 u = tb.w[t % Base<SC, I, TABLE>::kBases][j];
+      for (int j = 0; j < COUNT; ++j) {
+        double2 u = tb.get(t, j);
 #if defined(__HIP_DEVICE_COMPILE__)
         // a copy the optimizer cannot see through: the products of the base are
         // formed in each transform, not kept live from one to the next
-        asm volatile("" : "+v"(u.x), "+v"(u.y));
+        if constexpr (TW != kShared) asm volatile("" : "+v"(u.x), "+v"(u.y));
 #endif
         if constexpr (SIGN > 0) u.y = -u.y;
         p[j] = u;
       }
-      if constexpr (!TABLE) powers<R>(p[0], p);
-      dft<R, SIGN, true>(a, p);
+      if constexpr (products) {
+        static_for<1, R>([&](auto qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(qc)::value;
+          a[q] = mul(a[q], twiddle<R, q>(p));
+        });
+        dft_prime_factor<R, SIGN>(a);
+      } else {
+        if constexpr (TW == kSquares) powers<R>(p[0], p);
+        dft<R, SIGN, true>(a, p);
+      }
+    } else if constexpr (TW != kSquares) {
+      dft_prime_factor<R, SIGN>(a);
     } else {
-      dft<R, SIGN, false>(a, p);
+      dft<R, SIGN, false>(a, nullptr);
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) v[t + q * BPT] = a[q];

@@ -30,6 +30,7 @@ namespace lines {
 template <int L, int ELEM, bool TRANSPOSING>
 struct Tile {
   using SC = bfft::Sched<L, ELEM == 8 ? bfft::kLine64 : bfft::kLine32>;
+  static constexpr bfft::Twiddles kTw = ELEM == 8 ? bfft::kTable : bfft::kSquares;
   static constexpr int rows() {
     int t = ELEM == 4 ? 16 : 8;
     while (t > 1 && (t * SC::S > 640 || t * SC::kRow * 16 > 80 * 1024)) t /= 2;

@@ -119,6 +119,23 @@ __device__ __forceinline__ double2 post_step(double2 w) {
   else return half_turn<P, M>(w);
 }
 
+// The post-twiddles W^(s + S m), m < P / 2, of a thread: COUNT = 1 keeps W^s and
+// multiplies it by constants, which rounds once more; COUNT = P / 2 holds the
+// table's.
+template <int P, int S, int COUNT>
+struct Post {
+  double2 w[COUNT];
+  __device__ __forceinline__ void load(const double2* post, int s) {
+#pragma unroll
+    for (int m = 0; m < COUNT; ++m) w[m] = gload(post, s + S * m);
+  }
+  template <int M>
+  __device__ __forceinline__ double2 get() const {
+    if constexpr (COUNT == 1) return post_step<P, M>(w[0]);
+    else return w[M];
+  }
+};
+
 template <typename ST, int KIND, int L>
 struct Line {
   using SC = bfft::Sched<L, sizeof(ST) == 8 ? bfft::kLine64 : bfft::kLine32>;
@@ -132,8 +149,13 @@ struct Line {
   static constexpr int kRow = SC::kRow;
   static constexpr int kHalf = (L / 2) | 1;  // row of the r2c half exchange
   static constexpr bool kFull = NT == T * S;
-  static constexpr bool kTable = sizeof(ST) == 8;  // twiddle powers from the table
+  static constexpr bfft::Twiddles kTw = TL::kTw;
   static_assert(SC::valid() && SC::separable() && (N >= 2 || kZ), "schedule");
+  // FP64 rows of at most 12 points per thread hold the post-twiddles; at 16 and
+  // more (which would take 32 registers and more) the transform is exact enough
+  // (r2c of 64 values, 1e-16: 1.81 with constants, 1.73 held, 1.77 the generic
+  // kernel; of 2048 values 2.5 with constants, 3.4 the generic kernel)
+  using PT = Post<P, S, (kX && sizeof(ST) == 8 && P <= 12) ? P / 2 : 1>;
 
   // waves per SIMD that the registers are limited to: at 18 and 24 points per
   // thread the inverse x pass would take 258 registers and run alone on its
@@ -160,9 +182,9 @@ struct Line {
   static constexpr bool in_b() {
     return !kZ && (kFwd ? I == N - 1 : I == 0);
   }
-  bfft::Base<SC, 1, kTable> w1;
-  bfft::Base<SC, (N > 2 ? 2 : 1), kTable> w2;
-  bfft::Base<SC, (N > 3 ? 3 : 1), kTable> w3;
+  bfft::Base<SC, 1, kTw> w1;
+  bfft::Base<SC, (N > 2 ? 2 : 1), kTw> w2;
+  bfft::Base<SC, (N > 3 ? 3 : 1), kTw> w3;
   __device__ __forceinline__ void load_twiddles(const double2* tw) {
     w1.load(tw, in_b<1>() ? sB : sA);
     if constexpr (N > 2) w2.load(tw, in_b<2>() ? sB : sA);
@@ -172,14 +194,14 @@ struct Line {
   __device__ __forceinline__ void stage(double2 (&v)[P]) const {
     constexpr int SIGN = kFwd ? -1 : 1;
     if constexpr (I == 0) {
-      bfft::Base<SC, 0, kTable> none{};
-      bfft::stage<SC, 0, SIGN, kTable>(v, none);
+      bfft::Base<SC, 0, kTw> none{};
+      bfft::stage<SC, 0, SIGN, kTw>(v, none);
     } else if constexpr (I == 1) {
-      bfft::stage<SC, 1, SIGN, kTable>(v, w1);
+      bfft::stage<SC, 1, SIGN, kTw>(v, w1);
     } else if constexpr (I == 2) {
-      bfft::stage<SC, 2, SIGN, kTable>(v, w2);
+      bfft::stage<SC, 2, SIGN, kTw>(v, w2);
     } else {
-      bfft::stage<SC, 3, SIGN, kTable>(v, w3);
+      bfft::stage<SC, 3, SIGN, kTw>(v, w3);
     }
   }
   // exchange I; FROM_B / TO_B: the mappings it is written and read in
@@ -208,17 +230,17 @@ fft_line_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict
                 int nitems, FieldPtrs fields, ST* __restrict__ ws) {
   using LN = Line<ST, KIND, L>;
   using V = typename LN::V;
-  constexpr int P = LN::P, S = LN::S, T = LN::T, H = P / 2;
+  constexpr int P = LN::P, S = LN::S, H = P / 2;
   constexpr unsigned E = sizeof(V);
   __shared__ double2 lds[LN::TL::kLds];
   if (static_cast<int>(blockIdx.x) >= nitems) return;
   LN ln;
-  double2 wpost = bfft::c2(0.0, 0.0);
+  typename LN::PT wpost{};
   {
     // every item of the launch has this length, and the tables depend only on it
     const PatchDev* P0 = patches + items[0].patch;
     ln.load_twiddles(LN::kX ? P0->fx.tw : (LN::kY ? P0->fy.tw : P0->fz.tw));
-    if constexpr (LN::kX) wpost = gload(P0->post, ln.sB);
+    if constexpr (LN::kX) wpost.load(P0->post, ln.sB);
   }
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const WorkItem wi = items[xcd_local_order(it, nitems)];
@@ -293,7 +315,7 @@ fft_line_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict
         constexpr int m = decltype(mc)::value;
         const double2 a = up(xa[m]), b = up(xb[m]);
         // q = i conj(W^k) (a - conj b);  Z[k] = p + q, Z[L-k] = conj(p - q)
-        const double2 w = post_step<P, m>(wpost);
+        const double2 w = wpost.template get<m>();
         const double2 p = bfft::c2(a.x + b.x, a.y - b.y), d = bfft::c2(a.x - b.x, a.y + b.y);
         double2 z1 = bfft::c2(fma(-w.x, d.y, fma(w.y, d.x, p.x)), fma(w.x, d.x, fma(w.y, d.y, p.y)));
         double2 z2 = bfft::c2(fma(2.0, p.x, -z1.x), -fma(2.0, p.y, -z1.y));
@@ -323,12 +345,12 @@ fft_line_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict
       }
       __syncthreads();
       const unsigned offP = (rowB + (ln.sB == 0 ? L / 2 : L - ln.sB) * static_cast<unsigned>(C)) * E;
-      const double2 whalf = bfft::c2(0.5 * wpost.y, -0.5 * wpost.x);  // -i W^s / 2
       static_for<0, H>([&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value;
         const int slot = (m == 0 && ln.sB == 0) ? 0 : L / 2 - S * m - ln.sB;
         const double2 a = v[m], b = half[slot];
-        const double2 w = post_step<P, m>(whalf);
+        const double2 wm = wpost.template get<m>();
+        const double2 w = bfft::c2(0.5 * wm.y, -0.5 * wm.x);  // -i W^k / 2
         const double2 s = bfft::c2(a.x + b.x, a.y - b.y), d = bfft::c2(a.x - b.x, a.y + b.y);
         double2 x1 = bfft::c2(fma(-w.y, d.y, fma(w.x, d.x, 0.5 * s.x)),
                               fma(w.y, d.x, fma(w.x, d.y, 0.5 * s.y)));

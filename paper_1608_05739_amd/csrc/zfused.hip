@@ -24,18 +24,21 @@ Shape shape(int nz) {
   }
 }
 
-// LDS of the held inputs, per form.
+// LDS of the held inputs and of the twiddles, per form.
+template <int DIM, int SRC, int L, int ELEM>
+int form_bytes() {
+  using BU = Budget<DIM, SRC, L, ELEM>;
+  return BU::HELD_LDS * bfft::Sched<L, bfft::kFusedZ>::P * Tile<L>::NT * 2 * ELEM + BU::kTwiddles * 16;
+}
 template <int DIM, int L, int ELEM>
 int slots(int src) {
-  int n = 0;
   switch (src) {
-    case kVacuum: n = Budget<DIM, kVacuum, L, ELEM>::HELD_LDS; break;
-    case kRho: n = Budget<DIM, kRho, L, ELEM>::HELD_LDS; break;
-    case kJForm: n = Budget<DIM, kJForm, L, ELEM>::HELD_LDS; break;
-    case kPstdVacuum: n = Budget<DIM, kPstdVacuum, L, ELEM>::HELD_LDS; break;
-    default: n = Budget<DIM, kPstdJ, L, ELEM>::HELD_LDS; break;
+    case kVacuum: return form_bytes<DIM, kVacuum, L, ELEM>();
+    case kRho: return form_bytes<DIM, kRho, L, ELEM>();
+    case kJForm: return form_bytes<DIM, kJForm, L, ELEM>();
+    case kPstdVacuum: return form_bytes<DIM, kPstdVacuum, L, ELEM>();
+    default: return form_bytes<DIM, kPstdJ, L, ELEM>();
   }
-  return n * bfft::Sched<L, bfft::kFusedZ>::P * Tile<L>::NT * 2 * ELEM;
 }
 template <int L>
 int slots_of(int precision, int ndim, int src) {

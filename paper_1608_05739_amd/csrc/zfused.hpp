@@ -56,10 +56,13 @@ struct Budget {
   using SC = bfft::Sched<L, bfft::kFusedZ>;
   static constexpr int NIN = inputs(DIM, SRC);
   static constexpr int kTwo = ELEM == 4 ? 264 : 230;  // estimates up to which two waves pay
+  // double2 elements of a workgroup's LDS copy of the twiddles
+  static constexpr int kCopy = ELEM == 8 ? bfft::shared_offset<SC>(SC::N) : 0;
   // held inputs, the transform, the rest
   static constexpr int regs(int held) { return held * SC::P * ELEM / 2 + 7 * SC::P + 60; }
   static constexpr int lds_wave(int in_lds) {
-    return (SC::kRow * 16 * 64 + SC::S - 1) / SC::S + in_lds * SC::P * 64 * 2 * ELEM;
+    return (SC::kRow * 16 * 64 + SC::S - 1) / SC::S + in_lds * SC::P * 64 * 2 * ELEM +
+           kCopy * 16 * 64 / Tile<L>::NT;
   }
   // fewest inputs in LDS that leave the others (the outputs among them) within
   // the limit, -1: none
@@ -73,8 +76,14 @@ struct Budget {
   static constexpr int HELD_LDS = two ? held_lds(kTwo, 8) : (one >= 0 ? one : 0);
   static constexpr bool kPrefetch = !two || regs(NIN - HELD_LDS + 1) <= kTwo;
   static constexpr int waves = two ? 2 : 1;
-  // FP64: the twiddle powers of every stage from the table, where they fit
-  static constexpr bool kTable = ELEM == 8 && regs(NIN - HELD_LDS) + 36 <= (two ? kTwo : 480);
+  // FP64 storage: the twiddles in registers where radices are powers of two and
+  // their three per stage fit (2D rho form, 1024 points: 93 us, 98 from LDS), else
+  // in LDS (2D J form of 1728 x 1152, 12 points per thread: 145 us, 159 folded and
+  // from registers)
+  static constexpr bool kHeld = SC::P == 8 && regs(NIN - HELD_LDS) + 36 <= (two ? kTwo : 480);
+  static constexpr bfft::Twiddles kTw =
+      ELEM == 4 ? bfft::kSquares : (kHeld ? bfft::kTable : bfft::kShared);
+  static constexpr int kTwiddles = kTw == bfft::kShared ? kCopy : 0;
 };
 
 bool supported(int precision, int ndim, int src, int nz);

@@ -20,7 +20,7 @@ template <typename ST, int SRC, int L>
 constexpr int z_lds() {
   using LN = ZLine<ST, 2, SRC, L>;
   static_assert(LN::NT == kFamilyBlock, "one workgroup size in a family");
-  return LN::T * LN::SC::kRow + (LN::kSlots * sizeof(typename LN::V) + 15) / 16;
+  return LN::kLds;
 }
 template <typename ST, int SRC, int FAM>
 constexpr int family_lds() {
@@ -50,7 +50,7 @@ template <typename ST, int SRC, int L>
 __device__ __forceinline__ void z_item(int set, const PatchDev* P, const WorkItem& wi, ST* ws,
                                        const Physics& ph, double2* lds) {
   ZLine<ST, 2, SRC, L> ln;
-  ln.load_twiddles(P->fz.tw);
+  ln.load_twiddles(P->fz.tw, lds);
   if (set == 0) z_set<ST, 2, SRC, L, 0>(ln, P, wi, ws, ph, lds);
   else z_set<ST, 2, SRC, L, 1>(ln, P, wi, ws, ph, lds);
 }

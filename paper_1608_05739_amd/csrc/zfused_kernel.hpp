@@ -90,17 +90,20 @@ struct ZLine {
   using V = typename Store<ST>::V;
   static constexpr int P = SC::P, S = SC::S, N = SC::N, T = TL::T, NT = TL::NT;
   static constexpr bool kFull = NT == T * S;
-  static constexpr bool kTable = BU::kTable;
+  static constexpr bfft::Twiddles kTw = BU::kTw;
   static constexpr bool kWave = SC::kWave && kFull;
   static constexpr int kSlots = BU::HELD_LDS * P * NT;  // thread slots of held inputs (V)
+  // LDS in double2: the rows, the slots, the copy of the twiddles
+  static constexpr int kTwiddlesAt = T * SC::kRow + (kSlots * static_cast<int>(sizeof(V)) + 15) / 16;
+  static constexpr int kLds = kTwiddlesAt + BU::kTwiddles;
   static_assert(SC::valid() && SC::separable() && N >= 2, "schedule");
 
   int g, s;
   bool live;
-  bfft::Base<SC, 1, kTable> w1;
-  bfft::Base<SC, (N > 2 ? 2 : 1), kTable> w2;
-  bfft::Base<SC, (N > 3 ? 3 : 1), kTable> w3;
-  bfft::Base<SC, (N > 4 ? 4 : 1), kTable> w4;
+  bfft::Base<SC, 1, kTw> w1;
+  bfft::Base<SC, (N > 2 ? 2 : 1), kTw> w2;
+  bfft::Base<SC, (N > 3 ? 3 : 1), kTw> w3;
+  bfft::Base<SC, (N > 4 ? 4 : 1), kTw> w4;
 
   __device__ __forceinline__ ZLine() {
     const int tid = threadIdx.x;
@@ -109,7 +112,13 @@ struct ZLine {
     g = t / S;
     s = t % S;
   }
-  __device__ __forceinline__ void load_twiddles(const double2* tw) {
+  // (kShared: the copy is written by the whole workgroup, ends with a barrier)
+  __device__ __forceinline__ void load_twiddles(const double2* tw, double2* lds) {
+    if constexpr (kTw == bfft::kShared) {
+      bfft::fill_shared<SC>(lds + kTwiddlesAt, tw, threadIdx.x, NT);
+      __syncthreads();
+      tw = lds + kTwiddlesAt;
+    }
     w1.load(tw, s);
     if constexpr (N > 2) w2.load(tw, s);
     if constexpr (N > 3) w3.load(tw, s);
@@ -118,16 +127,16 @@ struct ZLine {
   template <int I, int SIGN>
   __device__ __forceinline__ void stage(double2 (&v)[P]) const {
     if constexpr (I == 0) {
-      bfft::Base<SC, 0, kTable> none{};
-      bfft::stage<SC, 0, SIGN, kTable>(v, none);
+      bfft::Base<SC, 0, kTw> none{};
+      bfft::stage<SC, 0, SIGN, kTw>(v, none);
     } else if constexpr (I == 1) {
-      bfft::stage<SC, 1, SIGN, kTable>(v, w1);
+      bfft::stage<SC, 1, SIGN, kTw>(v, w1);
     } else if constexpr (I == 2) {
-      bfft::stage<SC, 2, SIGN, kTable>(v, w2);
+      bfft::stage<SC, 2, SIGN, kTw>(v, w2);
     } else if constexpr (I == 3) {
-      bfft::stage<SC, 3, SIGN, kTable>(v, w3);
+      bfft::stage<SC, 3, SIGN, kTw>(v, w3);
     } else {
-      bfft::stage<SC, 4, SIGN, kTable>(v, w4);
+      bfft::stage<SC, 4, SIGN, kTw>(v, w4);
     }
   }
   template <int SIGN, int I = 0>
@@ -282,12 +291,12 @@ __global__ void __launch_bounds__((ZLine<ST, DIM, SRC, L>::NT))
 fft_z_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict__ items, int nitems,
              ST* __restrict__ ws, Physics ph) {
   using LN = ZLine<ST, DIM, SRC, L>;
-  __shared__ double2 lds[LN::T * LN::SC::kRow + (LN::kSlots * sizeof(typename LN::V) + 15) / 16];
+  __shared__ double2 lds[LN::kLds];
   constexpr int kSets = DIM == 2 ? 2 : 1;
   const int nwork = kSets * nitems;
   if (static_cast<int>(blockIdx.x) >= nwork) return;
   LN ln;
-  ln.load_twiddles(patches[items[0].patch].fz.tw);  // one length per launch
+  ln.load_twiddles(patches[items[0].patch].fz.tw, lds);  // one length per launch
   for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
     const WorkItem wi = items[w / kSets];
     const PatchDev* P = patches + wi.patch;
