@@ -90,39 +90,49 @@ __host__ __device__ inline void psatd_sincos(double h, double* s_out, double* c_
   *c_out = ((quad + 1) & 2) ? -cv : cv;
 }
 
-// sqrt(x) and 1 / sqrt(x) (0 and 0 at x = 0) from one reciprocal square root:
-// a coupled Newton iteration from the hardware estimate (2^-24 relative), then
-// the residual of each result, which leaves both within one unit of the last
-// place.  A correctly rounded square root and a division take 26 instructions
-// per mode instead of these 12.
-__host__ __device__ inline void psatd_roots(double x, double* root, double* inverse) {
+// An estimate of 1 / sqrt(x), x > 0 (the hardware's is within 2^-23).
+__host__ __device__ inline double psatd_rsqrt_estimate(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const double y = __builtin_amdgcn_rsq(x);
+  return __builtin_amdgcn_rsq(x);
+#else
+  return 1.0 / std::sqrt(x);
+#endif
+}
+
+// sqrt(x), and 1 / sqrt(x) to 2^-45, from an estimate y of 1 / sqrt(x) within
+// 2^-22 (0 and 0 at x = 0).  One step of the coupled iteration for g = sqrt(x)
+// and h = 1 / (2 sqrt(x)) (Goldschmidt's), then g is corrected by its residual:
+// the error before that rounding is the square of 2^-45, so that g is the
+// correctly rounded root but for about one argument in 2^38.
+__host__ __device__ inline void psatd_roots(double x, double y, double* root, double* inverse) {
   double g = x * y, h = 0.5 * y;
   const double e = fma(-h, g, 0.5);
   g = fma(g, e, g);
   h = fma(h, e, h);
   g = fma(fma(-g, g, x), h, g);
-  double r = h + h;
-  r = fma(fma(-g, r, 1.0), r, r);
-#else
-  const double g = std::sqrt(x), r = 1.0 / g;
-#endif
   *root = x > 0.0 ? g : x;  // (a NaN stays one)
-  *inverse = x > 0.0 ? r : 0.0;
+  *inverse = x > 0.0 ? h + h : 0.0;
 }
 
-// The coefficients of a mode with wavenumber squared K2.
+// 1 / a from an estimate r within 2^-40: one Newton step, whose rounding is that
+// of the quotient in the same way.
+__host__ __device__ inline double psatd_refine_inverse(double a, double r) {
+  return fma(fma(-a, r, 1.0), r, r);
+}
+
+// The coefficients of a mode with wavenumber squared K2.  K and 2 / theta carry
+// the rounding of a square root and a division; both come from one reciprocal
+// square root, at 12 instructions per mode instead of 26.
 __host__ __device__ inline Coef psatd_coef(double K2, double dt, double c, double eps0,
                                            double scale) {
   double K, rK;
-  psatd_roots(K2, &K, &rK);
+  psatd_roots(K2, psatd_rsqrt_estimate(K2), &K, &rK);
   const double half = 0.5 * c * dt;  // theta / 2 = half K
   const double h = half * K;
   const double th = 2.0 * h;
   double sh, ch;
   psatd_sincos(h, &sh, &ch);
-  const double ih = rK * (1.0 / half);
+  const double ih = (h > 0.0) ? psatd_refine_inverse(h, rK * (1.0 / half)) : 0.0;
   const double sinc_h = (h > 0.0) ? sh * ih : 1.0;
   const double sinc_th = sinc_h * ch;  // sin(th)/th = (2 sh ch)/(2 h)
   // Both forms are evaluated and one is selected: no divergent branch.
