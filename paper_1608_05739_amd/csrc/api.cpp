@@ -1278,17 +1278,35 @@ bool earlier_fixed_line_choice(const psatd_plan_s* plan, const Pass& c, const Ch
   return false;
 }
 
-// The same for the z pass: one wave of 64 / S lines per item, FP32, up to 512
-// points (3D: only powers of two).
-bool earlier_fixed_z_choice(const psatd_plan_s* plan, const Choice& ch) {
+// The same for the z pass (one wave of 64 / S lines per item, FP32 storage): 2D
+// lengths 2^k and 3 2^k up to 512 in the vacuum forms, 3D lengths 2^k up to 512
+// in the PSATD forms.  The 2D pass was launched per length, with the grid codes
+// that set_grid takes; the 3D pass saved its workgroups (of four waves): one wave
+// per item, or k per CU.  *grid becomes the grid that the choice has now: that
+// code, or in 3D the default.
+bool earlier_fixed_z_choice(const psatd_plan_s* plan, const Choice& ch, int* grid) {
   if (ch.type != kWaveZ || ch.ct != 0 || ch.mpt != 0 || ch.ppt != 0) return false;
   if (plan->cfg.precision != PSATD_FP32) return false;
-  int rows = 0;
+  const bool pstd = src_is_pstd(plan->src_form);
+  if (plan->ndim == 2 ? src_has_j(plan->src_form) : pstd) return false;
+  int rows = 0, items = 0;
   for (const PatchDev& P : plan->host_patches) {
-    if (P.nz > 512 || (P.nz % 3 != 0 && (P.nz & (P.nz - 1)) != 0)) return false;
-    rows = std::max(rows, 64 * (P.nz % 3 == 0 ? 12 : 8) / P.nz);
+    const bool three = P.nz % 3 == 0;
+    const int part = three ? P.nz / 3 : P.nz;
+    if (P.nz < 32 || P.nz > 512 || (part & (part - 1)) != 0 || (three && plan->ndim == 3)) return false;
+    const int per_wave = 64 * (three ? 12 : 8) / P.nz;
+    rows = std::max(rows, per_wave);
+    items += (P.mx * P.ny + per_wave - 1) / per_wave;
   }
-  return ch.lines == rows;
+  if (ch.lines != rows) return false;
+  *grid = ch.grid;
+  if (plan->ndim == 3 && ch.grid >= 0) {
+    const int full = (items + 3) / 4;
+    bool offered = ch.grid == full;
+    for (int k : {1, 2, 4, 8}) offered = offered || (ch.grid == k * plan->num_cus && ch.grid < full);
+    if (offered) *grid = -1;
+  }
+  return true;
 }
 
 // Apply the choices of a tuning string (from psatd_plan_tuning of a plan with
@@ -1302,22 +1320,22 @@ psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice)
     Pass& ps = plan->passes[i];
     const Choice& ch = choice[i];
     std::vector<Cand> cands = pass_candidates(plan, ps);
-    int pick = -1;
+    int pick = -1, grid = ch.grid;
     for (size_t ci = 0; ci < cands.size() && pick < 0; ++ci) {
       const Pass& c = cands[ci].pass;
       if ((c.type == ch.type && ch.ct == 0 && c.lines == ch.lines && c.mpt == ch.mpt &&
            c.ppt == ch.ppt) ||
           (c.type == kWaveX && earlier_fixed_line_choice(plan, c, ch)) ||
-          (c.type == kWaveZ && earlier_fixed_z_choice(plan, ch)))
+          (c.type == kWaveZ && earlier_fixed_z_choice(plan, ch, &grid)))
         pick = static_cast<int>(ci);
     }
     if (pick < 0)
       return fail(PSATD_ERR_INVALID_ARG,
                   std::string("tuning: no such kernel choice for pass ") + ps.name);
     Cand& c = cands[pick];
-    if (ch.grid >= 0) {
+    if (grid >= 0) {
       const std::vector<int> grids = grid_choices(plan, c.pass);
-      if (std::find(grids.begin(), grids.end(), ch.grid) == grids.end())
+      if (std::find(grids.begin(), grids.end(), grid) == grids.end())
         return fail(PSATD_ERR_INVALID_ARG, std::string("tuning: grid not offered for pass ") + ps.name);
     }
     if (!plan->dry) {
@@ -1327,8 +1345,8 @@ psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice)
       if (d) plan->extra_items.push_back(d);
     }
     ps = c.pass;
-    if (ch.grid >= 0) set_grid(plan, ps, ch.grid);
-    ps.grid_choice = ch.grid;
+    if (grid >= 0) set_grid(plan, ps, grid);
+    ps.grid_choice = grid;
     ps.tuning_applied = true;
   }
   return PSATD_OK;

@@ -96,3 +96,40 @@ def test_tuning_choice_not_offered_is_rejected():
         with pytest.raises(pk.PsatdError) as ei:
             pk.Plan([p], tuning=t)
         assert ei.value.status == -1 and "tuning" in str(ei.value), t
+
+
+def _z(info):
+    return [ln for ln in info.splitlines() if ln.strip().startswith("z_fused")][0]
+
+
+@pytest.mark.parametrize("shape,text", [
+    # strings of autotuned 3D plans whose z pass saved a number of workgroups
+    ((512, 512, 512), "7,0,16,0,0,8;7,0,8,0,0,0;6,0,1,0,0,256;7,0,8,0,0,8;7,0,16,0,0,8"),
+    ((1024, 1024, 512), "7,0,8,0,0,0;7,0,8,0,0,4;6,0,1,0,0,2048;7,0,8,0,0,0;7,0,8,0,0,0"),
+    # (one wave of 8 lines per item, four waves per workgroup: 32 x 32 lines)
+    ((64, 32, 64), "7,0,64,0,0,0;7,0,64,0,0,0;6,0,8,0,0,32;7,0,64,0,0,0;7,0,64,0,0,0"),
+])
+def test_3d_choices_with_an_earlier_z_grid_still_apply(shape, text):
+    say(f"tuning: earlier 3D z grid {shape}")
+    p = pk.Patch(3, shape, (1.0, 1.0, 1.0), 0.5)
+    now = pk.Plan([p], source_mode="rho", allocate_workspace=False)
+    default_grid = _z(now.info)
+    now.close()
+    again = pk.Plan([p], source_mode="rho", allocate_workspace=False, tuning="psatd-tuning-1;" + text)
+    assert _z(again.info) == default_grid + " (tuning applied)"
+    assert again.tuning.split(";")[3].endswith(",-1")
+    again.close()
+
+
+def test_earlier_choices_that_never_existed_are_rejected():
+    say("tuning: choices no earlier version had")
+    for shape, mode, text in [
+            # a 3D grid of workgroups that was not offered, a form and lengths without the kernel
+            ((64, 32, 64), "rho", "7,0,64,0,0,0;7,0,64,0,0,0;6,0,8,0,0,31;7,0,64,0,0,0;7,0,64,0,0,0"),
+            ((64, 32, 96), "rho", "7,0,64,0,0,0;7,0,64,0,0,0;6,0,8,0,0,-1;7,0,64,0,0,0;7,0,64,0,0,0"),
+            ((64, 1, 64), "rho", "7,0,64,0,0,0;6,0,8,0,0,0;7,0,64,0,0,0"),
+            ((64, 1, 72), "vacuum", "7,0,64,0,0,0;6,0,10,0,0,0;7,0,64,0,0,0")]:
+        p = pk.Patch(3 if shape[1] > 1 else 2, shape, (1.0, 1.0, 1.0), 0.5)
+        with pytest.raises(pk.PsatdError) as ei:
+            pk.Plan([p], source_mode=mode, tuning="psatd-tuning-1;" + text)
+        assert ei.value.status == -1 and "tuning" in str(ei.value) and "z_fused" in str(ei.value), text
