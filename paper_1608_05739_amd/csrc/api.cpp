@@ -1189,18 +1189,16 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
     add(make_fixed_line_pass(ps.line_kind, plan, ps.comps, its), its);
   }
   if (linelike || ps.type == kFused || ps.type == kWaveZ) {
-    for (int m : vars) {
-      for (int R : {1, 2, 4, 8, 16, 32}) {
-        std::vector<WorkItem> its;
-        Pass c;
-        if (linelike) {
-          c = make_line_pass(ps.line_kind, plan, ps.comps, its, R, m);
-        } else if (make_fused_pass(plan, its, &c, R, m) != PSATD_OK) {
-          continue;
-        }
-        add(c, its);
-      }
-    }
+    auto generic = [&](int R, int m) {
+      std::vector<WorkItem> its;
+      Pass c;
+      if (linelike) c = make_line_pass(ps.line_kind, plan, ps.comps, its, R, m);
+      else if (make_fused_pass(plan, its, &c, R, m) != PSATD_OK) return;
+      add(c, its);
+    };
+    generic(0, 0);  // the generic kernels' own default
+    for (int m : vars)
+      for (int R : {1, 2, 4, 8, 16, 32}) generic(R, m);
   }
   return cands;
 }

@@ -133,3 +133,22 @@ def test_earlier_choices_that_never_existed_are_rejected():
         with pytest.raises(pk.PsatdError) as ei:
             pk.Plan([p], source_mode=mode, tuning="psatd-tuning-1;" + text)
         assert ei.value.status == -1 and "tuning" in str(ei.value) and "z_fused" in str(ei.value), text
+
+
+@pytest.mark.parametrize("shape,precision", [((108, 1, 54), "fp64"), ((96, 1, 36), "fp32")])
+def test_default_tiles_of_the_generic_kernels_still_apply(shape, precision):
+    # plain z passes, whose generic default tile (54 and 48 lines) is no other
+    # candidate's: plans saved it while the generic kernels ran these lengths by default
+    say(f"tuning: generic defaults {shape} {precision}")
+    p = pk.Patch(2, shape, (1.0, 1.0, 1.0), 0.5)
+    generic = pk.Plan([p], precision=precision, path="plain", generic_kernels=True)
+    z = generic.tuning.split(";")[2]
+    plain = pk.Plan([p], precision=precision, path="plain")
+    now = plain.tuning.split(";")
+    assert z.split(",")[0] == "0" and int(z.split(",")[2]) > 32 and now[2].split(",")[0] == "7"
+    text = ";".join(now[:2] + [z] + now[3:])
+    again = pk.Plan([p], precision=precision, path="plain", tuning=text)
+    assert _passes(again.info)[1] == _passes(generic.info)[1]
+    assert again.tuning == text
+    for plan in (generic, plain, again):
+        plan.close()
