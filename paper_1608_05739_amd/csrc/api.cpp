@@ -826,21 +826,52 @@ Pass make_fast_pass(PassType type, const psatd_plan_s* plan, const std::vector<i
   return ps;
 }
 
-// The fused z pass with compile-time lengths (zfused.hpp) takes the plan if
-// every z length is compiled for its form.  Grids of at most 4 columns (nx <= 8)
-// with 2D lines of 1024 points and more keep the generic kernel: they are not
-// physical runs but what exercises its modes-per-thread fallbacks for long
-// lines (it is the slower one there too: 43 against 26 us at 1024 points with
-// sources, 145 against 40 at 4096).
-constexpr int kFewColumns = 5;
+// The fused z pass with compile-time lengths (zfused.hpp) can take the plan if
+// every z length is compiled for its form.
 bool fixed_z_eligible(const psatd_plan_s* plan) {
   const psatd_config& c = plan->cfg;
   if ((c.flags & PSATD_FLAG_GENERIC_KERNELS) || c.path != PSATD_PATH_FUSED) return false;
-  for (const PatchDev& P : plan->host_patches) {
+  for (const PatchDev& P : plan->host_patches)
     if (!zfused::supported(c.precision, plan->ndim, plan->src_form, P.nz)) return false;
-    if (plan->ndim == 2 && P.nz >= 1024 && P.mx < kFewColumns) return false;
-  }
   return true;
+}
+
+// Plans that it could take and that run the generic kernel by default (the
+// autotuner and saved choices have both).
+//
+// 3D lines at 12 points per thread, all inputs of a line one after the other in
+// one wave per SIMD: a chain of 12 to 17 transforms of 2 to 3 us.  The generic
+// kernel transforms the inputs together and is done in one round while its
+// workgroups do not outnumber the CUs: 96 points, rho form FP32, 2048 lines 34
+// against 47 us, 3072 lines (two rounds) 61 against 48; 216 points, vacuum FP64,
+// 768 lines 31 against 42, 1024 lines 55 against 42.  The J form in FP64, whose
+// nine inputs of 12 points spill, takes longer than two rounds and more: 96 points
+// 32768 lines 500 against 588, 288 points 4608 lines (six rounds) 302 against 321,
+// 6144 lines 407 against 347.  (Below 64 lines there is nothing to share out and
+// nothing a field solver does: 39 against 31 us at 36 points, not distinguished.)
+//
+// 2D grids of at most 4 columns with lines of 1024 points and more: not physical
+// runs, kept where the choices of modes per thread of the generic kernel are
+// taken by default (it is the slower one: 43 against 26 us at 1024 points with
+// sources, 145 against 40 at 4096).
+bool generic_z_by_default(const psatd_plan_s* plan) {
+  if (plan->ndim == 2)
+    return std::any_of(plan->host_patches.begin(), plan->host_patches.end(),
+                       [](const PatchDev& P) { return P.nz >= 1024 && P.mx <= 4; });
+  long long lines = 0;
+  int longest = 0;
+  for (const PatchDev& P : plan->host_patches) {
+    if (zfused::points_per_thread(P.nz) != 12) return false;
+    lines += static_cast<long long>(P.mx) * P.ny;
+    longest = std::max(longest, P.nz);
+  }
+  if (lines < 64) return false;
+  std::vector<WorkItem> items;
+  Pass generic;
+  if (!fused_fits(plan, items) || make_fused_pass(plan, items, &generic) != PSATD_OK) return false;
+  const bool spills = plan->cfg.precision == PSATD_FP64 && plan->src_form == kJForm;
+  if (spills && longest < 288) return true;
+  return generic.nitems <= (spills ? 6 : 1) * plan->num_cus;
 }
 
 // Work items of up to zfused::lines_per_item() z lines, one launch per length,
@@ -1168,8 +1199,8 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
   // (line passes: also at both radix schedules, radix-4 stages at 4 points
   // per thread and radices up to 8 at 8; they round differently, and each
   // is checked against the oracle by the tests)
-  // (the z pass with compile-time lengths: also the generic fused pass, at
-  // every choice)
+  // (the fused z pass: the kernels with compile-time lengths where they apply,
+  // and the generic one at every choice)
   // (line passes: also the kernels with compile-time lengths where they apply)
   const bool linelike = ps.type == kLine || ps.type == kWaveX;
   std::vector<int> vars = {0};
@@ -1187,6 +1218,10 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
   if (linelike && ps.type != kWaveX && fixed_line_eligible(ps.line_kind, plan)) {
     std::vector<WorkItem> its;
     add(make_fixed_line_pass(ps.line_kind, plan, ps.comps, its), its);
+  }
+  if (ps.type == kFused && fixed_z_eligible(plan)) {
+    std::vector<WorkItem> its;
+    add(make_fixed_z_pass(plan, its), its);
   }
   if (linelike || ps.type == kFused || ps.type == kWaveZ) {
     auto generic = [&](int R, int m) {
@@ -1629,7 +1664,7 @@ psatd_status build_plan(psatd_plan_s* plan) {
     };
     plan->passes.push_back(line(kXFwd, in_comps));
   if (plan->ndim == 3) plan->passes.push_back(line(kYFwd, in_comps));
-  if (fixed_z_eligible(plan)) {
+  if (fixed_z_eligible(plan) && !generic_z_by_default(plan)) {
     plan->passes.push_back(make_fixed_z_pass(plan, items));
   } else if (cfg.path == PSATD_PATH_FUSED && fused_fits(plan, items)) {
     Pass fz;

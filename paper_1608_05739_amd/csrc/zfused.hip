@@ -53,6 +53,7 @@ bool supported(int precision, int ndim, int src, int nz) {
 }
 int lines_per_item(int nz) { return shape(nz).lines; }
 int block(int nz) { return shape(nz).block; }
+int points_per_thread(int nz) { return bfft::fused_radices(nz).P; }
 int lds_bytes(int precision, int ndim, int src, int nz) {
   switch (nz) {
 #define PSATD_Z_SLOTS(LEN) \

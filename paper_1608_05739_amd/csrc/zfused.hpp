@@ -89,6 +89,7 @@ struct Budget {
 bool supported(int precision, int ndim, int src, int nz);
 int lines_per_item(int nz);  // T
 int block(int nz);
+int points_per_thread(int nz);
 int lds_bytes(int precision, int ndim, int src, int nz);
 // Workgroups that give every set of every item its own.
 inline int workgroups(int ndim, int nitems) { return ndim == 2 ? 2 * nitems : nitems; }

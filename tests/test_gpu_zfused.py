@@ -117,3 +117,26 @@ def test_families_of_lengths_equal_patches_alone(precision, mode, graph):
         for a, b in zip(got, ref):
             d = torch.linalg.vector_norm(a[off:off + p.cells] - b[:p.cells])
             assert d <= bound * torch.linalg.vector_norm(b[:p.cells]), (p, float(d))
+
+
+def test_3d_saved_choice_of_the_other_z_kernel():
+    """96 x 64 x 64 runs the generic z kernel by default; a saved choice of the
+    compile-time one (32 lines per work item) applies, and agrees with it."""
+    import torch
+    p = pk.Patch(3, (64, 64, 96), (1 / 32,) * 3, 1 / 40)
+    plain = pk.Plan([p], source_mode="rho")
+    choices = plain.tuning.split(";")
+    assert choices[3].split(",")[0] == "1"
+    choices[3] = "6,0,32,0,0,-1"
+    other = pk.Plan([p], source_mode="rho", tuning=";".join(choices))
+    say("3D saved z choice")
+    out = []
+    for plan in (plain, other):
+        g = torch.Generator().manual_seed(3)
+        t = [torch.randn(plan.total_elements, generator=g).cuda() for _ in range(11)]
+        plan.push(t[0:3], t[3:6], t[6:9], t[9], t[10])
+        torch.cuda.synchronize()
+        out.append(torch.cat([x.double() for x in t[:6]]))
+        plan.close()
+    # the same FP64 arithmetic rounded to FP32 storage at the same places
+    assert torch.linalg.vector_norm(out[0] - out[1]) <= 5e-7 * torch.linalg.vector_norm(out[0])

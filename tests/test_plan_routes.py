@@ -1,0 +1,26 @@
+"""Which fused z kernel a plan runs by default (host-only planning): 3D lines at
+12 points per thread run the generic kernel while it is done in one round of
+workgroups."""
+
+import pytest
+
+import paper_1608_05739_amd as pk
+
+
+def z_kernel(shapes, **kw):
+    patches = [pk.Patch(3 if s[1] > 1 else 2, s, (1.0, 1.0, 1.0), 0.5) for s in shapes]
+    info = pk.describe_plan(patches, **kw)[1]
+    line = [ln for ln in info.splitlines() if ln.strip().startswith("z_fused")][0]
+    return "generic" if line.endswith("kernel=generic") else "fixed"
+
+
+@pytest.mark.parametrize("shape,precision,mode,want", [
+    ((64, 64, 96), "fp32", "rho", "generic"),     # 2048 lines: 205 workgroups
+    ((96, 64, 96), "fp32", "rho", "fixed"),       # 3072 lines: 308
+    ((48, 32, 216), "fp64", "vacuum", "generic"), ((128, 64, 216), "fp64", "vacuum", "fixed"),
+    ((256, 256, 96), "fp64", "j", "generic"), ((192, 96, 288), "fp64", "j", "fixed"),
+    ((64, 64, 64), "fp32", "rho", "fixed"), ((64, 64, 54), "fp32", "rho", "fixed"),
+    ((6, 6, 96), "fp32", "rho", "fixed")])
+def test_3d_lines_of_12_points_per_thread(shape, precision, mode, want):
+    assert z_kernel([shape], precision=precision, source_mode=mode) == want
+
