@@ -853,10 +853,10 @@ bool fixed_z_eligible(const psatd_plan_s* plan) {
 // 2D grids of at most 4 columns with lines of 1024 points and more: not physical
 // runs, kept where the choices of modes per thread of the generic kernel are
 // taken by default (it is the slower one: 43 against 26 us at 1024 points with
-// sources, 145 against 40 at 4096).
+// sources, 145 against 40 at 4096).  One patch of more columns ends it.
 bool generic_z_by_default(const psatd_plan_s* plan) {
   if (plan->ndim == 2)
-    return std::any_of(plan->host_patches.begin(), plan->host_patches.end(),
+    return std::all_of(plan->host_patches.begin(), plan->host_patches.end(),
                        [](const PatchDev& P) { return P.nz >= 1024 && P.mx <= 4; });
   long long lines = 0;
   int longest = 0;

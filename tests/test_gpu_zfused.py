@@ -119,6 +119,21 @@ def test_families_of_lengths_equal_patches_alone(precision, mode, graph):
             assert d <= bound * torch.linalg.vector_norm(b[:p.cells]), (p, float(d))
 
 
+@pytest.mark.parametrize("shape", [(1024, 8), (2048, 8), (4096, 4), (1536, 6), (3072, 2)])
+@pytest.mark.parametrize("form", ["rho", "J"])
+def test_long_lines_of_few_columns_in_a_batch(shape, form):
+    """1 to 4 columns leave most of a work item of long lines idle."""
+    w, other = fixtures.workload(1, shape=shape, steps=2), fixtures.workload(1, shape=(96, 54), steps=2)
+    w.patches, w.E0, w.B0 = w.patches + other.patches, w.E0 + other.E0, w.B0 + other.B0
+    w.schedule = w.schedule + other.schedule
+    plan = pk.Plan(w.patches, source_mode={"rho": "rho", "J": "j"}[form])
+    assert [ln for ln in plan.info.splitlines() if "z_fused" in ln][0].endswith("kernel=wave"), plan.info
+    plan.close()
+    say(f"few columns {shape} {form}")
+    err = compare(run_gpu(w, "fp32", "fused", 2, form=form), run_oracle(w, "fp32", 2, form=form))
+    assert err < TOL["fp32"]
+
+
 def test_3d_saved_choice_of_the_other_z_kernel():
     """96 x 64 x 64 runs the generic z kernel by default; a saved choice of the
     compile-time one (32 lines per work item) applies, and agrees with it."""

@@ -1,6 +1,6 @@
 """Which fused z kernel a plan runs by default (host-only planning): 3D lines at
 12 points per thread run the generic kernel while it is done in one round of
-workgroups."""
+workgroups, and one patch of few columns does not decide for a batch."""
 
 import pytest
 
@@ -24,3 +24,9 @@ def z_kernel(shapes, **kw):
 def test_3d_lines_of_12_points_per_thread(shape, precision, mode, want):
     assert z_kernel([shape], precision=precision, source_mode=mode) == want
 
+
+def test_few_columns_do_not_decide_for_a_batch():
+    for few in ((8, 1, 1024), (4, 1, 4096), (6, 1, 1536)):
+        assert z_kernel([few], source_mode="rho") == "generic"
+        assert z_kernel([few, (64, 1, 64)], source_mode="rho") == "fixed"
+        assert z_kernel([few, few], source_mode="rho") == "generic"
