@@ -250,7 +250,11 @@ const char* psatd_pass_name(psatd_plan_t plan, int32_t i);
 psatd_status psatd_pass_bytes(psatd_plan_t plan, int32_t i, double* bytes);
 
 /* Human-readable description of the chosen kernels, tiles and launch shapes
- * (NUL-terminated, truncated to len). */
+ * (NUL-terminated, truncated to len).  The first line ends with step=graph where
+ * psatd_push replays a captured graph (PSATD_FLAG_GRAPH and a pass of several
+ * launches), else step=kernels.  Per pass, kernel= is generic, 4096 (the 4096 x
+ * 4096 2D grid), or the kernels with compile-time lengths: wave with FP32 storage,
+ * compile-time with FP64. */
 psatd_status psatd_plan_info(psatd_plan_t plan, char* buf, size_t len);
 
 /* Free plan-owned device memory and the plan.  NULL is accepted. */

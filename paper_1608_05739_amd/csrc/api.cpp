@@ -1717,10 +1717,11 @@ psatd_status build_plan(psatd_plan_s* plan) {
   char buf[512];
   plan->info.clear();
   std::snprintf(buf, sizeof(buf),
-                "ndim=%d patches=%zu solver=%s precision=%s source=%d path=%s order=%d ws=%zu\n",
+                "ndim=%d patches=%zu solver=%s precision=%s source=%d path=%s order=%d ws=%zu step=%s\n",
                 plan->ndim, plan->host_patches.size(), pstd ? "pstd" : "psatd",
                 cfg.precision == PSATD_FP32 ? "fp32" : "fp64", cfg.source_mode,
-                cfg.path == PSATD_PATH_FUSED ? "fused" : "plain", cfg.order, plan->ws_bytes);
+                cfg.path == PSATD_PATH_FUSED ? "fused" : "plain", cfg.order, plan->ws_bytes,
+                replays_graph(plan) ? "graph" : "kernels");
   plan->info += buf;
   for (const Pass& ps : plan->passes) {
     std::snprintf(buf, sizeof(buf),
