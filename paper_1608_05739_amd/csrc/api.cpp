@@ -143,7 +143,7 @@ struct DeviceGuard {
 };
 
 enum PassType { kLine = 0, kFused = 1, kUpdate = 2, kFastXFwd = 3, kFastZ = 4, kFastXInv = 5,
-                kWaveZ = 6, kWaveX = 7 };
+                kFixedZ = 6, kFixedLine = 7 };
 
 // One launch of a pass compiled per length: the work items of one line length,
 // or of a family of z lengths.
@@ -432,7 +432,7 @@ bool fixed_line_eligible(int kind, const psatd_plan_s* plan) {
 Pass make_fixed_line_pass(int kind, const psatd_plan_s* plan, const std::vector<int>& comps,
                           std::vector<WorkItem>& items) {
   Pass ps;
-  ps.type = kWaveX;
+  ps.type = kFixedLine;
   ps.line_kind = kind;
   ps.name = line_pass_name(kind);
   const int prec = plan->cfg.precision;
@@ -692,7 +692,7 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
         return fail(PSATD_ERR_STATE, std::string(ps.name) + ": bad block size");
       continue;
     }
-    if (ps.type == kWaveX) {
+    if (ps.type == kFixedLine) {
       int L, nrows, A;
       fixed_line_geometry(ps.line_kind, P, &L, &nrows, &A);
       const int prec = plan->cfg.precision;
@@ -711,7 +711,7 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
         return fail(PSATD_ERR_STATE, std::string(ps.name) + " (fixed length): item outside its length's launch");
       continue;
     }
-    if (ps.type == kWaveZ) {
+    if (ps.type == kFixedZ) {
       if (!zfused::supported(plan->cfg.precision, P.ndim, plan->src_form, P.nz))
         return fail(PSATD_ERR_STATE, "z_fused (fixed length): z length not compiled");
       if (w.count < 1 || w.first < 0 || w.first + w.count > P.mx * P.ny ||
@@ -781,7 +781,7 @@ psatd_status verify_pass(const psatd_plan_s* plan, const Pass& ps, const WorkIte
 bool fast2d_eligible(const psatd_plan_s* plan) {
   const psatd_config& c = plan->cfg;
   if (c.flags & (PSATD_FLAG_GENERIC_KERNELS | PSATD_FLAG_PSTD)) return false;
-  if (!plan->maps.empty()) return false;  // only the generic x passes read through a map
+  if (!plan->maps.empty()) return false;  // these x passes do not read through a map
   if (plan->ndim != 2 || c.precision != PSATD_FP32 || c.path != PSATD_PATH_FUSED) return false;
   for (const PatchDev& P : plan->host_patches)
     if (P.nx != fast2d::kNX || P.nz != fast2d::kNZfast) return false;
@@ -878,7 +878,7 @@ bool generic_z_by_default(const psatd_plan_s* plan) {
 // or per family of lengths of which the plan has several (longest lines first).
 Pass make_fixed_z_pass(const psatd_plan_s* plan, std::vector<WorkItem>& items) {
   Pass ps;
-  ps.type = kWaveZ;
+  ps.type = kFixedZ;
   ps.name = "z_fused";
   const size_t first = items.size();
   const int prec = plan->cfg.precision;
@@ -989,13 +989,13 @@ psatd_status enqueue_pass(const psatd_plan_s* plan, const Pass& ps, const FieldP
       e = launch_update(plan->cfg.precision, plan->src_form, ps.shape, s, plan->d_patches,
                         ps.d_items, ps.nitems, ws, ph);
       break;
-    case kWaveX:
+    case kFixedLine:
       e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
         return lines::launch(ps.line_kind, plan->cfg.precision, sub.L, sub.shape.grid, t,
                              plan->d_patches, ps.d_items + sub.first, sub.nitems, f, ws);
       });
       break;
-    case kWaveZ:
+    case kFixedZ:
       e = for_subs(ps, s, fork, [&](const SubLaunch& sub, hipStream_t t) {
         if (sub.family)
           return zfused::launch_family(plan->cfg.precision, plan->src_form, sub.family, sub.shape.grid,
@@ -1202,9 +1202,9 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
   // (the fused z pass: the kernels with compile-time lengths where they apply,
   // and the generic one at every choice)
   // (line passes: also the kernels with compile-time lengths where they apply)
-  const bool linelike = ps.type == kLine || ps.type == kWaveX;
+  const bool linelike = ps.type == kLine || ps.type == kFixedLine;
   std::vector<int> vars = {0};
-  if (ps.type == kFused || ps.type == kWaveZ) vars = fused_mpt_choices(plan->cfg.precision, plan->ndim);
+  if (ps.type == kFused || ps.type == kFixedZ) vars = fused_mpt_choices(plan->cfg.precision, plan->ndim);
   if (linelike) vars = {4, kMaxPts};
   auto add = [&](Pass c, std::vector<WorkItem>& its) {
     for (const Cand& x : cands)
@@ -1215,7 +1215,7 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
     if (verify_pass(plan, c, its.data()) != PSATD_OK) return;
     cands.push_back(Cand{c, std::move(its)});
   };
-  if (linelike && ps.type != kWaveX && fixed_line_eligible(ps.line_kind, plan)) {
+  if (linelike && ps.type != kFixedLine && fixed_line_eligible(ps.line_kind, plan)) {
     std::vector<WorkItem> its;
     add(make_fixed_line_pass(ps.line_kind, plan, ps.comps, its), its);
   }
@@ -1223,7 +1223,7 @@ std::vector<Cand> pass_candidates(const psatd_plan_s* plan, const Pass& ps) {
     std::vector<WorkItem> its;
     add(make_fixed_z_pass(plan, its), its);
   }
-  if (linelike || ps.type == kFused || ps.type == kWaveZ) {
+  if (linelike || ps.type == kFused || ps.type == kFixedZ) {
     auto generic = [&](int R, int m) {
       std::vector<WorkItem> its;
       Pass c;
@@ -1285,7 +1285,7 @@ psatd_status upload_items(psatd_plan_s* plan, Cand& c, WorkItem** d) {
 }
 
 // A choice of the compile-time line kernels as earlier versions saved it, with
-// the tiles that those kernels had (type kWaveX: waves of up to 64 / S rows, or
+// the tiles that those kernels had (type kFixedLine: waves of up to 64 / S rows, or
 // type kLine with the compile-time flag: 512 threads of 6 or 8 points): it
 // selects the present ones.
 bool earlier_fixed_line_choice(const psatd_plan_s* plan, const Pass& c, const Choice& ch) {
@@ -1306,7 +1306,7 @@ bool earlier_fixed_line_choice(const psatd_plan_s* plan, const Pass& c, const Ch
     wave_rows = std::max(wave_rows, (per_wave <= 2 ? 8 : 4) * per_wave);
     block_rows = std::max(block_rows, std::min(512 * (L % 3 == 0 ? 6 : 8) / L, nlines));
   }
-  if (ch.type == kWaveX && ch.ct == 0) return in_wave && ch.lines == wave_rows;
+  if (ch.type == kFixedLine && ch.ct == 0) return in_wave && ch.lines == wave_rows;
   if (ch.type == kLine && ch.ct == 1) return in_block && ch.lines == block_rows;
   return false;
 }
@@ -1318,7 +1318,7 @@ bool earlier_fixed_line_choice(const psatd_plan_s* plan, const Pass& c, const Ch
 // per item, or k per CU.  *grid becomes the grid that the choice has now: that
 // code, or in 3D the default.
 bool earlier_fixed_z_choice(const psatd_plan_s* plan, const Choice& ch, int* grid) {
-  if (ch.type != kWaveZ || ch.ct != 0 || ch.mpt != 0 || ch.ppt != 0) return false;
+  if (ch.type != kFixedZ || ch.ct != 0 || ch.mpt != 0 || ch.ppt != 0) return false;
   if (plan->cfg.precision != PSATD_FP32) return false;
   const bool pstd = src_is_pstd(plan->src_form);
   if (plan->ndim == 2 ? src_has_j(plan->src_form) : pstd) return false;
@@ -1358,8 +1358,8 @@ psatd_status apply_tuning(psatd_plan_s* plan, const std::vector<Choice>& choice)
       const Pass& c = cands[ci].pass;
       if ((c.type == ch.type && ch.ct == 0 && c.lines == ch.lines && c.mpt == ch.mpt &&
            c.ppt == ch.ppt) ||
-          (c.type == kWaveX && earlier_fixed_line_choice(plan, c, ch)) ||
-          (c.type == kWaveZ && earlier_fixed_z_choice(plan, ch, &grid)))
+          (c.type == kFixedLine && earlier_fixed_line_choice(plan, c, ch)) ||
+          (c.type == kFixedZ && earlier_fixed_z_choice(plan, ch, &grid)))
         pick = static_cast<int>(ci);
     }
     if (pick < 0)
@@ -1728,7 +1728,7 @@ psatd_status build_plan(psatd_plan_s* plan) {
                   "  %-10s items=%d grid=%d block=%d lds=%zu mpt=%d ppt=%d lines=%d bytes=%.0f kernel=%s%s\n",
                   ps.name, ps.nitems, ps.shape.grid, ps.shape.block, ps.shape.lds_bytes, ps.mpt,
                   ps.ppt, ps.lines, ps.bytes,
-                  (ps.type == kWaveZ || ps.type == kWaveX)
+                  (ps.type == kFixedZ || ps.type == kFixedLine)
                       ? (cfg.precision == PSATD_FP32 ? "wave" : "compile-time")
                       : (ps.type >= kFastXFwd ? "4096" : "generic"),
                   ps.tuning_applied ? " (tuning applied)" : (ps.tuned_ms >= 0.0 ? " (autotuned)" : ""));

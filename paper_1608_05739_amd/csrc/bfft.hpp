@@ -322,8 +322,6 @@ struct Radices {
 // bases, 24.24.2 would hold 13).
 constexpr Radices line_radices(int L) {
   switch (L) {
-    case 16: return {8, 2, {2, 8}};
-    case 18: return {18, 1, {18}};
     case 24: return {12, 2, {2, 12}};
     case 32: return {8, 2, {4, 8}};
     case 36: return {12, 2, {3, 12}};

@@ -613,7 +613,7 @@ struct ZCol {
     return v;
   }
   __device__ __forceinline__ Coef coef(double kzv) const {
-    return psatd_coef(kx * kx + kzv * kzv, dt, c, eps0, scale);
+    return psatd_coef<float>(kx * kx + kzv * kzv, dt, c, eps0, scale);
   }
   __device__ __forceinline__ const float2* src(int comp) const { return col + comp * cs; }
   // Software pipeline: `pre` holds the loads issued one phase earlier.  Issue

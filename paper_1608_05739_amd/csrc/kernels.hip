@@ -419,7 +419,7 @@ __device__ __forceinline__ void fused_group(const PatchDev* P, const WorkItem& w
       if constexpr (src_is_pstd(SRC)) {
         pstd_update_mode<SRC>(kx, ky, kz, dt, ph.c, ph.eps0, P->inv_n, E, B, J, Eo, Bo);
       } else {
-        const Coef q = psatd_coef(kx * kx + ky * ky + kz * kz, dt, ph.c, ph.eps0, P->inv_n);
+        const Coef q = psatd_coef<S>(kx * kx + ky * ky + kz * kz, dt, ph.c, ph.eps0, P->inv_n);
         update_mode<SRC>(kx, ky, kz, q, ph.c, ph.eps0, dt, E, B, J, ro, rn, Eo, Bo);
       }
       static_for<0, Gr::nout>([&](auto oc) __attribute__((always_inline)) {
@@ -524,7 +524,7 @@ update_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict__
       if constexpr (src_is_pstd(SRC)) {
         pstd_update_mode<SRC>(kx, ky, kz, dt, ph.c, ph.eps0, P->inv_n, E, B, J, Eo, Bo);
       } else {
-        const Coef q = psatd_coef(kx * kx + ky * ky + kz * kz, dt, ph.c, ph.eps0, P->inv_n);
+        const Coef q = psatd_coef<S>(kx * kx + ky * ky + kz * kz, dt, ph.c, ph.eps0, P->inv_n);
         update_mode<SRC>(kx, ky, kz, q, ph.c, ph.eps0, dt, E, B, J, ro, rn, Eo, Bo);
       }
 #pragma unroll

@@ -99,19 +99,23 @@ __host__ __device__ inline double psatd_rsqrt_estimate(double x) {
 #endif
 }
 
-// sqrt(x), and 1 / sqrt(x) to 2^-45, from an estimate y of 1 / sqrt(x) within
-// 2^-22 (0 and 0 at x = 0).  One step of the coupled iteration for g = sqrt(x)
-// and h = 1 / (2 sqrt(x)) (Goldschmidt's), then g is corrected by its residual:
-// the error before that rounding is the square of 2^-45, so that g is the
-// correctly rounded root but for about one argument in 2^38.
+// sqrt(x) and 1 / sqrt(x) (0 and 0 at x = 0) from an estimate y of 1 / sqrt(x)
+// within 2^-22: one step of the coupled iteration for g = sqrt(x) and
+// h = 1 / (2 sqrt(x)) (Goldschmidt's), then each result is corrected by its
+// residual.  The error before that rounding is the square of 2^-45, so that the
+// results are the correctly rounded root and the correctly rounded inverse of that
+// root but for about one argument in 2^38.  A square root and a division take 26
+// instructions per mode instead of these 12.
 __host__ __device__ inline void psatd_roots(double x, double y, double* root, double* inverse) {
   double g = x * y, h = 0.5 * y;
   const double e = fma(-h, g, 0.5);
   g = fma(g, e, g);
   h = fma(h, e, h);
   g = fma(fma(-g, g, x), h, g);
+  double r = h + h;
+  r = fma(fma(-g, r, 1.0), r, r);
   *root = x > 0.0 ? g : x;  // (a NaN stays one)
-  *inverse = x > 0.0 ? h + h : 0.0;
+  *inverse = x > 0.0 ? r : 0.0;
 }
 
 // 1 / a from an estimate r within 2^-40: one Newton step, whose rounding is that
@@ -120,9 +124,12 @@ __host__ __device__ inline double psatd_refine_inverse(double a, double r) {
   return fma(fma(-a, r, 1.0), r, r);
 }
 
-// The coefficients of a mode with wavenumber squared K2.  K and 2 / theta carry
-// the rounding of a square root and a division; both come from one reciprocal
-// square root, at 12 instructions per mode instead of 26.
+// The coefficients of a mode with wavenumber squared K2, for fields stored as ST.
+// 2 / theta is a product of two inverses, each off by half a unit of the last
+// place; FP64 storage rounds it once, as a division does.  (FP32 storage does not
+// show it, and its kernels, which are full, spill with the step: 4096 x 4096 with
+// sources 1082 -> 1161 us, 64 patches with sources 274 -> 301.)
+template <typename ST>
 __host__ __device__ inline Coef psatd_coef(double K2, double dt, double c, double eps0,
                                            double scale) {
   double K, rK;
@@ -132,7 +139,8 @@ __host__ __device__ inline Coef psatd_coef(double K2, double dt, double c, doubl
   const double th = 2.0 * h;
   double sh, ch;
   psatd_sincos(h, &sh, &ch);
-  const double ih = (h > 0.0) ? psatd_refine_inverse(h, rK * (1.0 / half)) : 0.0;
+  double ih = rK * (1.0 / half);
+  if constexpr (sizeof(ST) == 8) ih = h > 0.0 ? psatd_refine_inverse(h, ih) : 0.0;
   const double sinc_h = (h > 0.0) ? sh * ih : 1.0;
   const double sinc_th = sinc_h * ch;  // sin(th)/th = (2 sh ch)/(2 h)
   // Both forms are evaluated and one is selected: no divergent branch.
@@ -272,7 +280,7 @@ __device__ __forceinline__ double2 add_r(double2 a, double s, double2 b) {
 // Advance one polarization set of one mode, in the component order of
 // Group<G, SRC>: in holds the set's inputs, the first three become the outputs.
 // `scale` is the 1/N of the inverse FFTs.
-template <int G, int SRC>
+template <typename ST, int G, int SRC>
 __device__ __forceinline__ void update_set(double kx, double kz, double dt, double c, double eps0,
                                            double scale, double2* in) {
   if constexpr (src_is_pstd(SRC)) {
@@ -296,7 +304,7 @@ __device__ __forceinline__ void update_set(double kx, double kz, double dt, doub
       in[2] = cscale(by, scale);
     }
   } else {
-    const Coef q = psatd_coef(kx * kx + kz * kz, dt, c, eps0, scale);
+    const Coef q = psatd_coef<ST>(kx * kx + kz * kz, dt, c, eps0, scale);
     const double cS = c * c * q.S;
     if constexpr (G == 0) {
       double2 e = cscale(in[0], q.C), bx = cscale(in[1], q.C), bz = cscale(in[2], q.C);

@@ -244,12 +244,12 @@ __device__ __forceinline__ void z_set(const ZLine<ST, DIM, SRC, L>& ln, const Pa
       else in[k] = up(slot[((k - NR) * NP + m) * LN::NT]);
     });
     if constexpr (DIM == 2) {
-      update_set<G, SRC>(kx, kzv[m], dt, ph.c, ph.eps0, scale, in);
+      update_set<ST, G, SRC>(kx, kzv[m], dt, ph.c, ph.eps0, scale, in);
 #pragma unroll
       for (int k = 0; k < 3; ++k) held[m].set(k, in[k]);
     } else {
       const double kz = kzv[m];
-      const Coef q = psatd_coef(kx * kx + ky * ky + kz * kz, dt, ph.c, ph.eps0, scale);
+      const Coef q = psatd_coef<ST>(kx * kx + ky * ky + kz * kz, dt, ph.c, ph.eps0, scale);
       double2 Eo[3], Bo[3];
       update_mode<SRC>(kx, ky, kz, q, ph.c, ph.eps0, dt, in, in + 3, in + 6, in[9], in[10], Eo, Bo);
 #pragma unroll

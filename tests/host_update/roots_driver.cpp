@@ -19,12 +19,13 @@ int main() {
     double root, inverse;
     psatd::psatd_roots(x, y, &root, &inverse);
     if (root != std::sqrt(x)) ++wrong_root;
+    if (inverse != 1.0 / root) ++wrong_inverse;
     const double half = factor(gen), h = root * half;
     if (psatd::psatd_refine_inverse(h, inverse * (1.0 / half)) != 1.0 / h) ++wrong_inverse;
   }
   double r0 = -1, i0 = -1;
   psatd::psatd_roots(0.0, INFINITY, &r0, &i0);
-  const psatd::Coef at0 = psatd::psatd_coef(0.0, 0.5, 2.0, 4.0, 0.25);
+  const psatd::Coef at0 = psatd::psatd_coef<double>(0.0, 0.5, 2.0, 4.0, 0.25);
   const bool zero = r0 == 0.0 && i0 == 0.0 && at0.C == 0.25 && at0.S == 0.125;
   std::printf("%lld of %d roots and %lld of %d inverses not correctly rounded, zero %s\n", wrong_root, n,
               wrong_inverse, n, zero ? "ok" : "wrong");
