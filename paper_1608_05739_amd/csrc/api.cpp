@@ -867,11 +867,12 @@ bool generic_z_by_default(const psatd_plan_s* plan) {
   }
   if (lines < 64) return false;
   std::vector<WorkItem> items;
-  Pass generic;
-  if (!fused_fits(plan, items) || make_fused_pass(plan, items, &generic) != PSATD_OK) return false;
+  if (!fused_fits(plan, items)) return false;
   const bool spills = plan->cfg.precision == PSATD_FP64 && plan->src_form == kJForm;
   if (spills && longest < 288) return true;
-  return generic.nitems <= (spills ? 6 : 1) * plan->num_cus;
+  Pass generic;
+  return make_fused_pass(plan, items, &generic) == PSATD_OK &&
+         generic.nitems <= (spills ? 6 : 1) * plan->num_cus;
 }
 
 // Work items of up to zfused::lines_per_item() z lines, one launch per length,

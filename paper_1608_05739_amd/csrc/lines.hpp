@@ -23,10 +23,13 @@ namespace lines {
 // elements are one run of 8 T (FP32) or 16 T bytes (FP64).  T is 16 or 8 (128
 // bytes) as long as two tiles fit a CU's LDS, and is halved until they do:
 // neighbouring tiles run on one XCD and complete the lines in its L2, and a
-// second tile on the CU is worth more than longer runs (1152 points, FP32: 3.4
-// and 3.0 TB/s with 64-byte runs and one tile per CU, 4.3 and 3.5 with two).
-// FP64 keeps 64 bytes where one tile fits (2048 points forward: 4.3 TB/s,
-// 2.8 with two tiles of 32-byte runs).
+// second tile on the CU is worth more than longer runs.  FP32 x passes of
+// grids of 4 M cells with sources, forward / inverse TB/s, two tiles of short runs
+// against one of runs twice or four times as long: 648 points (32 bytes) 3.9 / 3.5
+// and 2.7 / 2.6; 1152 points (32 bytes) 3.8 / 3.5 and 3.1 / 2.6; 1296 points (16
+// bytes) 3.4 / 2.7 and 2.6 / 2.5; 2048 points (16 bytes) 3.4 / 3.5 and 3.3 / 3.0.
+// FP64 keeps 64 bytes where one tile fits (2048 points forward: 4.0 TB/s, 2.8 with
+// two tiles of 32-byte runs).
 template <int L, int ELEM, bool TRANSPOSING>
 struct Tile {
   using SC = bfft::Sched<L, ELEM == 8 ? bfft::kLine64 : bfft::kLine32>;

@@ -119,15 +119,18 @@ __device__ __forceinline__ double2 post_step(double2 w) {
   else return half_turn<P, M>(w);
 }
 
-// The post-twiddles W^(s + S m), m < P / 2, of a thread: COUNT = 1 keeps W^s and
-// multiplies it by constants, which rounds once more; COUNT = P / 2 holds the
-// table's.
-template <int P, int S, int COUNT>
+// The post-twiddles W^(s + S m) (FWD: -i W^(s + S m) / 2), m < P / 2, of a thread:
+// COUNT = 1 keeps that of m = 0 and multiplies it by constants, which rounds once
+// more; COUNT = P / 2 holds the table's.
+template <int P, int S, int COUNT, bool FWD>
 struct Post {
   double2 w[COUNT];
   __device__ __forceinline__ void load(const double2* post, int s) {
 #pragma unroll
-    for (int m = 0; m < COUNT; ++m) w[m] = gload(post, s + S * m);
+    for (int m = 0; m < COUNT; ++m) {
+      const double2 v = gload(post, s + S * m);
+      w[m] = FWD ? bfft::c2(0.5 * v.y, -0.5 * v.x) : v;
+    }
   }
   template <int M>
   __device__ __forceinline__ double2 get() const {
@@ -155,7 +158,7 @@ struct Line {
   // more (which would take 32 registers and more) the transform is exact enough
   // (r2c of 64 values, 1e-16: 1.81 with constants, 1.73 held, 1.77 the generic
   // kernel; of 2048 values 2.5 with constants, 3.4 the generic kernel)
-  using PT = Post<P, S, (kX && sizeof(ST) == 8 && P <= 12) ? P / 2 : 1>;
+  using PT = Post<P, S, (kX && sizeof(ST) == 8 && P <= 12) ? P / 2 : 1, kFwd>;
 
   // waves per SIMD that the registers are limited to: at 18 and 24 points per
   // thread the inverse x pass would take 258 registers and run alone on its
@@ -349,8 +352,7 @@ fft_line_kernel(const PatchDev* __restrict__ patches, const WorkItem* __restrict
         constexpr int m = decltype(mc)::value;
         const int slot = (m == 0 && ln.sB == 0) ? 0 : L / 2 - S * m - ln.sB;
         const double2 a = v[m], b = half[slot];
-        const double2 wm = wpost.template get<m>();
-        const double2 w = bfft::c2(0.5 * wm.y, -0.5 * wm.x);  // -i W^k / 2
+        const double2 w = wpost.template get<m>();
         const double2 s = bfft::c2(a.x + b.x, a.y - b.y), d = bfft::c2(a.x - b.x, a.y + b.y);
         double2 x1 = bfft::c2(fma(-w.y, d.y, fma(w.x, d.x, 0.5 * s.x)),
                               fma(w.y, d.x, fma(w.x, d.y, 0.5 * s.y)));

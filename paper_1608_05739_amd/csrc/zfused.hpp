@@ -48,9 +48,11 @@ struct Tile {
 // where 256 registers each are enough -- with up to HELD_LDS inputs in LDS
 // slots of their thread, and without the next input's loads in flight where
 // those do not fit.  512^3 rho form (9 inputs in registers, 2 in LDS, no
-// prefetch, a few spills): 2.81 ms; one wave with 394 registers: 3.63 ms.  FP64
+// prefetch, a few spills): 2.9 ms; one wave with 394 registers: 3.63 ms.  FP64
 // takes the second wave only with room to spare: the 2D J form at 512 points
-// ran 51.8 us with it (spills) and 32.8 without (2048 x 512).
+// ran 51.8 us with it (spills) and 32.8 without (2048 x 512).  At 8 points per
+// thread that is every FP32 form and the 2D vacuum form in FP64; at 12 points the
+// 2D FP32 forms but rho.  The others run one wave per SIMD.
 template <int DIM, int SRC, int L, int ELEM>
 struct Budget {
   using SC = bfft::Sched<L, bfft::kFusedZ>;

@@ -12,12 +12,12 @@
 // allow.  Lines of up to 64 threads never leave their wave, so that their
 // exchanges need no workgroup barrier.
 //
-// Bound: the FP64 instructions of the transforms and of the update, at two
-// waves per SIMD.  Measured, z pass alone: 512^3 rho form FP32 4.43 -> 2.81 ms
-// (2.06 -> 3.25 TB/s; the kernel before accumulated the six outputs input by
+// Bound: the FP64 instructions of the transforms and of the update, at two waves
+// per SIMD or one (Budget).  Measured, z pass alone: 512^3 rho form FP32 4.43 ->
+// 2.89 ms (2.06 -> 3.16 TB/s; the kernel before accumulated the six outputs input by
 // input, rounding each contribution to FP32, at one wave per SIMD); 1152 x 1536
-// J form 192 -> 118 us, 216 x 96 x 144 vacuum 235 -> 86 us, 1024^2 rho FP64 99
-// -> 72 us, 128 x 192 x 256 rho FP64 470 -> 263 us (the generic kernel before).
+// J form 192 -> 90 us, 216 x 96 x 144 vacuum 235 -> 78 us, 1024^2 rho FP64 99
+// -> 51 us, 128 x 192 x 256 rho FP64 470 -> 253 us (the generic kernel before).
 #pragma once
 
 #include "update.hpp"
