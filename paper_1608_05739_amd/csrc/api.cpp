@@ -850,24 +850,42 @@ bool fixed_z_eligible(const psatd_plan_s* plan) {
 // 6144 lines 407 against 347.  (Below 64 lines there is nothing to share out and
 // nothing a field solver does: 39 against 31 us at 36 points, not distinguished.)
 //
+// 2D batches of narrow patches: a work item holds lines of one patch only, so that
+// patches of a few columns leave most of its threads idle, and once the chip is
+// full that is time.  The generic kernel's workgroups shrink to the lines they hold.  At most a quarter of the item lines in use and two
+// workgroups per CU (12 points per thread with sources) or four (else): 256 patches
+// of 16 x 96 rho form FP32 37 against 54 us, 512 of 8 x 108 49 against 135, 512 of
+// 16 x 64 33 against 43; 512 of 96 x 64 the compile-time kernel.
+//
 // 2D grids of at most 4 columns with lines of 1024 points and more: not physical
 // runs, kept where the choices of modes per thread of the generic kernel are
 // taken by default (it is the slower one: 43 against 26 us at 1024 points with
 // sources, 145 against 40 at 4096).  One patch of more columns ends it.
 bool generic_z_by_default(const psatd_plan_s* plan) {
-  if (plan->ndim == 2)
-    return std::all_of(plan->host_patches.begin(), plan->host_patches.end(),
-                       [](const PatchDev& P) { return P.nz >= 1024 && P.mx <= 4; });
-  long long lines = 0;
-  int longest = 0;
-  for (const PatchDev& P : plan->host_patches) {
-    if (zfused::points_per_thread(P.nz) != 12) return false;
-    lines += static_cast<long long>(P.mx) * P.ny;
-    longest = std::max(longest, P.nz);
-  }
-  if (lines < 64) return false;
   std::vector<WorkItem> items;
   if (!fused_fits(plan, items)) return false;
+  bool twelve = true, few = true;
+  long long lines = 0, slots = 0, nitems = 0;
+  int longest = 0;
+  for (const PatchDev& P : plan->host_patches) {
+    const long long n = static_cast<long long>(P.mx) * P.ny;
+    const int T = zfused::lines_per_item(P.nz);
+    const long long k = (n + T - 1) / T;
+    lines += n;
+    nitems += k;
+    slots += k * T;
+    longest = std::max(longest, P.nz);
+    twelve = twelve && zfused::points_per_thread(P.nz) == 12;
+    few = few && P.nz >= 1024 && P.mx <= 4;
+  }
+  if (plan->ndim == 2) {
+    if (few) return true;
+    if (src_is_pstd(plan->src_form)) return false;
+    const int per_cu = twelve && src_has_j(plan->src_form) ? 2 : 4;
+    return 4 * lines <= slots &&
+           zfused::workgroups(2, static_cast<int>(nitems)) >= per_cu * plan->num_cus;
+  }
+  if (!twelve || lines < 64) return false;
   const bool spills = plan->cfg.precision == PSATD_FP64 && plan->src_form == kJForm;
   if (spills && longest < 288) return true;
   Pass generic;

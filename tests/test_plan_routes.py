@@ -1,6 +1,7 @@
 """Which fused z kernel a plan runs by default (host-only planning): 3D lines at
 12 points per thread run the generic kernel while it is done in one round of
-workgroups, and one patch of few columns does not decide for a batch."""
+workgroups, large batches of narrow patches run it, and one patch of few columns
+does not decide for a batch."""
 
 import pytest
 
@@ -30,3 +31,12 @@ def test_few_columns_do_not_decide_for_a_batch():
         assert z_kernel([few], source_mode="rho") == "generic"
         assert z_kernel([few, (64, 1, 64)], source_mode="rho") == "fixed"
         assert z_kernel([few, few], source_mode="rho") == "generic"
+
+
+@pytest.mark.parametrize("nx,nz,patches,mode,want", [
+    (16, 96, 256, "rho", "generic"), (16, 96, 255, "rho", "fixed"), (16, 96, 511, "vacuum", "fixed"),
+    (16, 96, 512, "vacuum", "generic"), (18, 96, 512, "rho", "fixed"), (16, 64, 256, "rho", "fixed"),
+    (16, 64, 512, "rho", "generic"), (64, 64, 512, "rho", "fixed")])
+def test_large_batches_of_narrow_patches(nx, nz, patches, mode, want):
+    # 32 lines per work item at 64 and 96 points: 8 columns fill a quarter of one
+    assert z_kernel([(nx, 1, nz)] * patches, source_mode=mode) == want
